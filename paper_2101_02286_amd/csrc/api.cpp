@@ -123,7 +123,7 @@ struct Arena {
   size_t add(const void *src, size_t bytes) {
     const size_t off = (host.size() + 255) & ~size_t(255);
     host.resize(off + bytes);
-    if (bytes) std::memcpy(host.data() + off, src, bytes);
+    if (src && bytes) std::memcpy(host.data() + off, src, bytes);  // (no source: filled in later)
     return off;
   }
   template <typename V> size_t add(const std::vector<V> &v) { return add(v.data(), v.size() * sizeof(V)); }
@@ -145,6 +145,15 @@ cb_status upload(Plan &p) {
     so[i].c32 = ar.add(to_f32(s.coef));
     so[i].r32 = ar.add(to_f32(s.red));
     so[i].w32 = ar.add(to_f32(s.wf));
+  }
+  struct WinOff { size_t c, g, i; };
+  WinOff wo[2] = {};
+  WinLayout *wins[2] = {&p.wx, &p.ws};
+  for (int i = 0; i < 2; ++i) {
+    const WinLayout &w = *wins[i];
+    if (!w.M) continue;
+    const bool f64 = p.precision == CB_FP64;
+    wo[i] = {f64 ? ar.add(w.coef) : ar.add(to_f32(w.coef)), f64 ? ar.add(w.g) : ar.add(to_f32(w.g)), ar.add(w.gidx)};
   }
   const size_t o_bands = ar.add(p.bands);
   size_t o_wg = 0, o_sr = 0, o_sroff = 0, o_ltut = 0, o_ro = 0, o_src = 0, o_mats = 0, o_bfun = 0;
@@ -198,6 +207,11 @@ cb_status upload(Plan &p) {
   }
   p.dev_base = d;
   p.dev_bytes = (int64_t)ar.host.size();
+  for (int i = 0; i < 2; ++i) {
+    wins[i]->d_coef = base + wo[i].c;
+    wins[i]->d_g = base + wo[i].g;
+    wins[i]->d_gidx = reinterpret_cast<const int *>(base + wo[i].i);
+  }
   p.segdev = reinterpret_cast<SegDev *>(base + o_segdev);
   p.d_bands = reinterpret_cast<const double *>(base + o_bands);
   if (p.P > 1) {
@@ -336,6 +350,153 @@ void residual_bands(const Plan &p, LineArgs &a) {
   const size_t mid = (size_t)(p.n / 2) * W;  // an interior row: every entry present
   for (int o = 0; o < W; ++o) a.bands[o] = p.bands[mid + o];
   a.bands_row = (p.desc.per_row || !p.desc.cyclic) ? p.d_bands : nullptr;
+}
+
+// ------------------------------------------------------ windowed launch --
+// Arguments, workgroup size, grid and LDS of a windowed-lane launch.
+struct WinLaunch {
+  WinArgs a;
+  const WinKernel *k;
+  int threads;
+  int64_t blocks;
+  size_t lds;
+};
+
+// Sets up the windowed-lane launch of these lines; false when the plan has no
+// such layout for their row stride or it does not fit this call (lines whose
+// neighbours are not adjacent in memory; a line in several workgroups that is
+// solved in place, since a workgroup reads rows that another one writes).
+// How: a solve or fused derivative by itself, as an item of a batched launch
+// (plain solves take the identity stencil), or the same data moved without
+// arithmetic; whether a call runs this way does not depend on it.
+enum WinHow { WIN_SINGLE, WIN_BATCH, WIN_COPY };
+bool win_config(const Plan &p, const Geo &g, const double *in, double *out, const cb_stencil *st, WinHow how,
+                WinLaunch &w) {
+  const int mode = g.rs == 1 ? MODE_X : MODE_S;
+  const WinLayout &wl = mode == MODE_X ? p.wx : p.ws;
+  if (!wl.M || g.nlines >= (int64_t(1) << 31)) return false;
+  const int Q = st ? (st->lo >= -2 && st->hi <= 2 ? 2 : 3) : (how == WIN_BATCH ? 2 : 0);
+  const int prec = p.precision == CB_FP64 ? 0 : (p.refine_iters > 0 ? 2 : 1);
+  w.k = find_win_kernel(p.R, wl.M, prec, mode, Q, wl.uniform != 0);
+  const WinKernel *wide = find_win_kernel(p.R, wl.M, prec, mode, 3, wl.uniform != 0);  // the most LDS
+  if (how == WIN_COPY) w.k = find_win_copy_kernel(wl.M, mode, wl.uniform != 0);
+  if (!w.k || !wide) return false;
+  WinArgs &a = w.a;
+  std::memset(&a, 0, sizeof(a));
+  a.in = in;
+  a.out = out;
+  a.nlines = g.nlines;
+  a.su = g.su;
+  a.sv = g.sv;
+  a.rs = g.rs;
+  a.one = -1;
+  int64_t nu = g.nu;
+  if (mode == MODE_S) {  // pairs of adjacent lines
+    if (g.su != 1) return false;
+    const bool contiguous = g.nlines <= g.nu || g.sv == g.nu;
+    if (contiguous) nu = g.nlines;
+    const int64_t pairs = (nu + 1) / 2;
+    a.one = nu % 2 ? (int)(pairs - 1) : -1;
+    a.nlines = contiguous ? pairs : pairs * (g.nlines / g.nu);
+    a.su = 2;
+    nu = pairs;
+  }
+  a.nudiv = make_divmagic((uint32_t)nu);
+  a.n = (int)g.n;
+  a.L = wl.L;
+  a.base = wl.base;
+  a.extra = wl.extra;
+  a.D = wl.D;
+  a.acyclic = p.desc.cyclic ? 0 : 1;
+  a.Lw = wl.L;
+  a.Lc = wl.L;
+  a.nch = 1;
+  a.refine_iters = p.refine_iters;
+  // lanes whose solution a launch gets wrong at either end of a window: D + 1
+  // per solve, and one more for each residual between two solves
+  const int halo = (p.refine_iters + 1) * (wl.D + 1) + p.refine_iters;
+  // equal chunks of the line's lanes with their halo, at most `most` lanes in
+  // all; one for each partition where the plan was asked for several
+  const int parts = p.desc.partitions > 1 ? p.desc.partitions : 0;
+  auto split = [&](int most) {
+    const int own = parts ? (wl.L + parts - 1) / parts : most - 2 * halo;
+    if (own + 2 * halo > most || (own < 8 && own < wl.L)) return false;
+    a.H = halo;
+    a.nch = (wl.L + own - 1) / own;
+    a.Lc = (wl.L + a.nch - 1) / a.nch;
+    a.nch = (wl.L + a.Lc - 1) / a.Lc;
+    a.Lw = a.Lc + 2 * halo;
+    return a.nch == 1 || in != out;
+  };
+  // rows that are whole 128-byte lines stream past the caches; others share
+  // lines with their neighbours, which the caches then serve (the strided
+  // tenth-order derivative on planes of odd extent: 247 -> 285 GDOF/s)
+  const bool whole = g.su == 1 && (g.nlines <= g.nu || (g.nu % 16 == 0 && g.sv % 16 == 0)) && g.rs % 16 == 0 &&
+                     (uintptr_t)in % 128 == 0 && (uintptr_t)out % 128 == 0;
+  if (mode == MODE_X) {
+    const int QP = (Q + 1) & ~1;
+    if (parts || wl.L > 64 || wl.L * wl.M != a.n) {
+      if (!split(64) || a.n < (halo + 1) * wl.M + 4) return false;
+    }
+    int waves = p.R == 1 ? 4 : 1;  // (wider bands: one measured 2-10 % faster, tridiagonal ones four)
+    w.threads = 64 * waves;
+    a.lpw = 64 / a.Lw;
+    a.linv = (65536 + a.Lw - 1) / a.Lw;
+    a.W = waves * a.lpw;
+    a.pitch = (a.Lw * (wl.M + 1) + 2 * QP + 4) & ~1;
+    a.nt = a.H == 0 ? 1 : 0;
+    a.chunk_fast = 1;
+  } else {
+    // Pairs of lines per tile.  Lines of up to 64 lanes lie in one workgroup:
+    // 32 pairs while that makes at most 256 threads or, on rows that are not
+    // whole cache lines, 1024 (wider segments share fewer lines: n = 431 on odd
+    // planes 252 -> 285 GDOF/s; not with 8-row lanes beyond 96 rows), else 16.
+    // Longer ones take 32-lane chunks: 32 pairs for tridiagonal lines on such
+    // rows (n = 8192 along y of 63-line planes 206 -> 255), else 16; partitions
+    // that were asked for take 16 pairs and up to 64 lanes.
+    const bool chunks = parts || wl.L * 16 > 1024;
+    int W = wl.L * 32 <= (whole ? 256 : 1024) ? 32 : 16;
+    if (!whole && wl.M == 8 && wl.L > 12) W = 16;
+    if (chunks) W = !whole && p.R == 1 && !parts ? 32 : 16;
+    if (chunks) {
+      if (!split(parts ? 1024 / W : 32) || a.Lw > wl.L) return false;
+    }
+    a.W = W;
+    a.lgW = ilog2(W);
+    w.threads = (a.Lw * W + 63) / 64 * 64;
+    a.nt = whole && !chunks ? 1 : 0;  // (neighbouring chunks share their halo rows)
+    // chunks of a line one after the other, or on rows that are not whole cache
+    // lines the same chunk of neighbouring lines (n = 4096 on 89-line planes:
+    // y 198 -> 211, z 224 -> 255 GDOF/s; 64-line planes y 357 against 398)
+    a.chunk_fast = whole ? 1 : 0;
+  }
+  auto lds_of = [&](const WinKernel *k) {
+    return ((size_t)k->lds * a.W * (a.Lw + 2 * a.D + 2) + (size_t)a.W * a.pitch + (wl.uniform ? 0 : wl.g.size())) *
+           sizeof(double);
+  };
+  w.lds = lds_of(w.k);
+  if (w.threads > w.k->max_threads || lds_of(wide) + 64 > lds_cap()) return false;
+  const int64_t ltiles = (a.nlines + a.W - 1) / a.W;
+  w.blocks = ltiles * a.nch;
+  if (w.blocks > 0x7fffffff) return false;
+  a.ltiles = (uint32_t)ltiles;
+  // (chunks of one line, or of neighbouring ones, on one XCD share its L2)
+  a.xcds = mode == MODE_S && a.nch > 1 && p.desc.tile_order != 1 ? xcd_count() : tile_xcds(p, mode, 2 * a.W, g);
+  a.coef = wl.d_coef;
+  a.g = wl.d_g;
+  a.gidx = wl.d_gidx;
+  a.gcount = (int)wl.g.size();
+  if (st) stencil_q(st, a.stc);
+  else a.stc[3] = 1.0;
+  const size_t mid = (size_t)(p.n / 2) * (2 * p.R + 1);  // an interior row: every entry present
+  for (int o = 0; o < 2 * p.R + 1; ++o) a.bands[o] = p.bands[mid + o];
+  return true;
+}
+
+cb_status launch_win(WinLaunch &w, hipStream_t stream) {
+  void *args[] = {&w.a};
+  const hipError_t e = hipLaunchKernel(w.k->fn, dim3((unsigned)w.blocks), dim3(w.threads), args, w.lds, stream);
+  return e == hipSuccess ? CB_OK : hip_fail(e, "kernel launch");
 }
 
 // --------------------------------------------------------- P = 1 launch --
@@ -674,6 +835,19 @@ cb_status launch_wg(const Plan &p, const Geo &g, const double *in, double *out, 
   return CB_OK;
 }
 
+// One solve or fused derivative: windowed lanes where the plan and the call
+// allow them, else the partitioned or the whole-line kernels.  A call that
+// would need more partition scratch than a fixed buffer holds is refused
+// whichever way it would run.
+cb_status launch(const Plan &p, const Geo &g, const double *in, double *out, const cb_stencil *st, hipStream_t stream,
+                 const FixedScratch *fs) {
+  const Plan *parts = p.P > 1 ? &p : (g.rs != 1 ? p.strided_wg.get() : nullptr);
+  const bool refused = fs && parts && wg_scratch_bytes(*parts, g.nlines) > fs->bytes;
+  WinLaunch w;
+  if (!refused && win_config(p, g, in, out, st, WIN_SINGLE, w)) return launch_win(w, stream);
+  return p.P > 1 ? launch_wg(p, g, in, out, st, stream, fs) : launch_line(p, g, in, out, st, stream, fs);
+}
+
 cb_status check_plan_for_solve(cb_plan_t plan) {
   if (!plan) return fail(CB_ERR_INVALID_ARG, "plan is NULL");
   if (plan->p.host_only || !plan->p.dev_base)
@@ -699,8 +873,7 @@ cb_status solve_entry(cb_plan_t plan, const cb_grid *grid, int32_t axis, const d
   // partitioned refinement re-reads b after x has been written
   if (b == x && plan->p.P > 1 && plan->p.refine_iters > 0)
     return fail(CB_ERR_UNSUPPORTED, "partitioned FP32 + refinement solves need b and x apart (not in place)");
-  if (plan->p.P == 1) return launch_line(plan->p, g, b, x, nullptr, static_cast<hipStream_t>(stream), fs);
-  return launch_wg(plan->p, g, b, x, nullptr, static_cast<hipStream_t>(stream), fs);
+  return launch(plan->p, g, b, x, nullptr, static_cast<hipStream_t>(stream), fs);
 }
 
 cb_status set_error(cb_status s, const char *msg) { return fail(s, msg); }
@@ -814,10 +987,7 @@ cb_status cb_apply_derivative(cb_plan_t plan, const cb_stencil *stencil, const c
   if (g.nlines == 0) return CB_OK;  // empty grid: nothing is read or written
   if (!f || !out) return fail(CB_ERR_INVALID_ARG, "f and out must be non-NULL");
   if (overlap(f, out, span_elems(grid))) return fail(CB_ERR_INVALID_ARG, "f and out overlap");
-  if (plan->p.P != 1) {
-    return launch_wg(plan->p, g, f, out, stencil, static_cast<hipStream_t>(stream), nullptr);
-  }
-  return launch_line(plan->p, g, f, out, stencil, static_cast<hipStream_t>(stream), nullptr);
+  return launch(plan->p, g, f, out, stencil, static_cast<hipStream_t>(stream), nullptr);
 }
 
 cb_status cb_copy_lines(cb_plan_t plan, const cb_grid *grid, int32_t axis, const double *in, double *out,
@@ -831,6 +1001,10 @@ cb_status cb_copy_lines(cb_plan_t plan, const cb_grid *grid, int32_t axis, const
   if (g.nlines == 0) return CB_OK;
   if (!in || !out) return fail(CB_ERR_INVALID_ARG, "in and out must be non-NULL");
   if (overlap(in, out, span_elems(grid))) return fail(CB_ERR_INVALID_ARG, "in and out overlap");
+  const bool in_parts = g.rs != 1 && plan->p.strided_wg;  // refused by launch_line
+  WinLaunch w;
+  if (!in_parts && win_config(plan->p, g, in, out, nullptr, WIN_COPY, w))
+    return launch_win(w, static_cast<hipStream_t>(stream));
   return launch_line(plan->p, g, in, out, nullptr, static_cast<hipStream_t>(stream), nullptr, true);
 }
 
@@ -849,15 +1023,13 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
   std::vector<WgItem> wg_items;
   size_t sc_next = align256(batch_items_offset((size_t)n_items) + (size_t)n_items * sizeof(BatchItemDev));
   struct Cls {
-    int R, M, fp;
-    bool uni, ilu;
     const void *fn;
     int threads;
     size_t lds;
+    bool win;
     std::vector<int> members;
   };
   std::vector<Cls> cls;
-  std::vector<int> cls_of(n_items);
   std::vector<BatchItemDev> tab(n_items);
   std::vector<int64_t> ntiles(n_items);
   for (int i = 0; i < n_items; ++i) {
@@ -876,6 +1048,24 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
       if (!p.desc.cyclic) return fail(CB_ERR_INVALID_ARG, "cb_batch_build: a stencil needs a cyclic plan");
     }
     if (g.nlines >= (int64_t(1) << 31)) return fail(CB_ERR_UNSUPPORTED, "cb_batch_build: more than 2^31 lines");
+    WinLaunch w;
+    if (win_config(p, g, it.in, it.out, it.stencil, WIN_BATCH, w)) {
+      WinItemDev d;
+      std::memset(&d, 0, sizeof(d));
+      d.a = w.a;
+      d.threads = w.threads;
+      std::memcpy(&tab[i], &d, sizeof(d));
+      ntiles[i] = w.blocks;
+      // items of one instance share a launch: unit-stride ones have one
+      // workgroup size, strided ones take the largest of theirs
+      int c = 0;
+      while (c < (int)cls.size() && cls[c].fn != w.k->batch_fn) ++c;
+      if (c == (int)cls.size()) cls.push_back(Cls{w.k->batch_fn, 0, 0, true, {}});
+      cls[c].threads = std::max(cls[c].threads, w.threads);
+      cls[c].lds = std::max(cls[c].lds, w.lds);
+      cls[c].members.push_back(i);
+      continue;
+    }
     if (const Plan *wp = batch_wg_plan(p, g)) {  // its own phase launches, scratch in the workspace
       WgItem w;
       w.plan = it.plan;
@@ -890,7 +1080,6 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
       w.sc_off = sc_next;
       sc_next += align256(w.sc_bytes);
       wg_items.push_back(w);
-      cls_of[i] = -1;
       continue;
     }
     // the plan's lane layout for this item's row stride, as a single launch uses
@@ -994,10 +1183,9 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
     ntiles[i] = (g.nlines + W - 1) / W;
     int c = 0;
     while (c < (int)cls.size() && !(cls[c].fn == fn && cls[c].threads == nt)) ++c;
-    if (c == (int)cls.size()) cls.push_back(Cls{p.R, sp.M, fp, uni, ilu, fn, nt, 0, {}});
+    if (c == (int)cls.size()) cls.push_back(Cls{fn, nt, 0, false, {}});
     cls[c].lds = std::max(cls[c].lds, lds);
     cls[c].members.push_back(i);
-    cls_of[i] = c;
   }
   for (int i = 0; i < n_items; ++i)
     for (int j = i + 1; j < n_items; ++j)
@@ -1009,12 +1197,24 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
   size_t slot = 0;
   for (size_t c = 0; c < cls.size(); ++c) {
     int64_t tiles = 0;
+    // (a class's entries lie one after the other from its first slot, windowed
+    // ones, which are smaller, closer together)
+    char *entry = host.data() + batch_items_offset(n_items) + slot * sizeof(BatchItemDev);
     for (int i : cls[c].members) {
-      tab[i].tile_begin = tiles;
+      if (cls[c].win) {
+        WinItemDev d;
+        std::memcpy(&d, &tab[i], sizeof(d));
+        d.tile_begin = tiles;
+        std::memcpy(entry, &d, sizeof(d));
+        entry += sizeof(d);
+      } else {
+        tab[i].tile_begin = tiles;
+        std::memcpy(entry, &tab[i], sizeof(BatchItemDev));
+        entry += sizeof(BatchItemDev);
+      }
       tiles += ntiles[i];
-      std::memcpy(host.data() + batch_items_offset(n_items) + (slot++) * sizeof(BatchItemDev), &tab[i],
-                  sizeof(BatchItemDev));
     }
+    slot += cls[c].members.size();
     BatchHdr h;
     std::memset(&h, 0, sizeof(h));
     h.n_items = (int)cls[c].members.size();

@@ -2,6 +2,7 @@
 // stores of a one-partition launch with the stencil and the solve left out,
 // so that the solve's own memory access pattern can be timed alone.
 #include "line.h"
+#include "win.h"
 
 namespace cb {
 
@@ -17,6 +18,23 @@ static const LineKernel kCopy[] = {
 
 const LineKernel *find_copy_kernel(int M, int mode, bool uni) {
   for (const auto &k : kCopy)
+    if (k.M == M && k.mode == mode && k.uni == uni) return &k;
+  return nullptr;
+}
+
+// The same for windowed lanes.
+#define CB_WIN_COPY(M, MODE, UNI)                                                    \
+  {1, M, 0, MODE, 0, UNI, win_max_threads<MODE>(), win_planes(1, 0, false, MODE) * win_lines(MODE), \
+   (const void *)&k_win<1, M, double, false, MODE, 0, UNI, true>, nullptr}
+static const WinKernel kWinCopy[] = {
+    CB_WIN_COPY(8, MODE_X, true),  CB_WIN_COPY(10, MODE_X, true),  CB_WIN_COPY(12, MODE_X, true),
+    CB_WIN_COPY(16, MODE_X, true), CB_WIN_COPY(20, MODE_X, true),  CB_WIN_COPY(24, MODE_X, true),
+    CB_WIN_COPY(8, MODE_S, true),  CB_WIN_COPY(12, MODE_S, true),  CB_WIN_COPY(16, MODE_S, true),
+    CB_WIN_COPY(8, MODE_S, false), CB_WIN_COPY(12, MODE_S, false), CB_WIN_COPY(16, MODE_S, false),
+};
+
+const WinKernel *find_win_copy_kernel(int M, int mode, bool uni) {
+  for (const auto &k : kWinCopy)
     if (k.M == M && k.mode == mode && k.uni == uni) return &k;
   return nullptr;
 }

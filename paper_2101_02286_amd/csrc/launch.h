@@ -45,6 +45,29 @@ struct LineArgs {
   const double *bands_row;   // per-row bands [n][2R+1] or nullptr
 };
 
+// Arguments of a windowed-lane launch (win.h).
+struct WinArgs {
+  const double *in;
+  double *out;
+  int64_t nlines, su, sv, rs;
+  DivMagic nudiv;            // line -> (u, v)
+  int n, L, base, extra;     // the line's lanes (WinLayout)
+  int Lw, H, Lc, nch;        // lanes of a line in one workgroup, halo lanes per side, lanes stored, chunks per line
+  int D, acyclic, W;         // window half-width; lines (strided rows: pairs of lines) per tile
+  int lgW, one;              // strided rows: log2 W; the pair of a row of lines that holds one line, or -1
+  int lpw;                   // unit-stride rows: lines per wavefront
+  uint32_t linv;             // ... and ceil(2^16 / Lw)
+  int pitch;                 // ... and tile words per line
+  int chunk_fast;            // chunks of a line are consecutive tiles
+  uint32_t ltiles;           // line tiles (chunk slowest)
+  int xcds, refine_iters;
+  int nt, gcount;            // streaming loads and stores; values in g
+  const void *coef, *g;
+  const int *gidx;
+  double stc[7];             // stencil coefficients for q = -3..3
+  double bands[2 * kMaxR + 1];
+};
+
 struct WgArgs {
   const double *in;
   double *out;
@@ -96,6 +119,14 @@ struct LineKernel {
   int max_threads;  // workgroup size bound of the instance
   const void *fn;
 };
+struct WinKernel {
+  int R, M, prec, mode, Q;   // prec: 0 FP64, 1 FP32, 2 FP32 + refinement
+  bool uni;
+  int max_threads;
+  int lds;                   // LDS doubles per slot
+  const void *fn;
+  const void *batch_fn;      // batched form (Q = 2 and 3)
+};
 struct WgKernel {
   int R, M, mode, Q;
   bool ilu;                        // lane interiors by banded elimination
@@ -127,6 +158,14 @@ struct BatchKernel {
   int mode, Q, threads;  // row mode, stencil half-width and workgroup size of the instance
   const void *fn;
 };
+// Work-table entry of a windowed-lane item (in the slot of a BatchItemDev).
+struct WinItemDev {
+  WinArgs a;
+  int64_t tile_begin;
+  int threads;  // of the item's tiles; the launch's workgroups may have more
+  int pad;
+};
+static_assert(sizeof(WinItemDev) <= sizeof(BatchItemDev), "windowed items must fit the work table");
 static_assert(sizeof(BatchHdr) <= 64, "batch queue header must fit its 64-byte slot");
 
 // A caller-owned device buffer that P > 1 launches use for their partition
@@ -152,6 +191,8 @@ const BatchKernel *find_batch_kernel(int R, int M, int fp32, bool uni, bool ilu,
 const WgKernel *find_wg_kernel(int R, int M, int mode, int Q, bool ilu);
 // FP32 + refinement instances of the partitioned kernels (wg_fp32.hip)
 const WgKernel *find_wg32_kernel(int R, int M, int mode, int Q, bool ilu);
+const WinKernel *find_win_kernel(int R, int M, int prec, int mode, int Q, bool uni);
+const WinKernel *find_win_copy_kernel(int M, int mode, bool uni);
 const void *stencil_kernel();
 
 }  // namespace cb

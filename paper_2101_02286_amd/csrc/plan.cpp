@@ -8,6 +8,8 @@
 // reduced system (Sec. 4 Algorithms 1-4).
 #include "plan.h"
 
+#include "winplan.h"
+
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -893,7 +895,66 @@ int auto_refine_iters(const cb_plan_desc &d) {
   return k;
 }
 
-cb_status build_plan(const cb_plan_desc &d, Plan &p, std::string &msg) {
+// Windowed lanes of a plan with constant bands whose launch shape is left to
+// the library (p.wx: unit-stride launches, p.ws: strided ones).
+//
+// Unit-stride lines (a wavefront holds up to 64 lanes of one or more lines):
+// lines that also split into 2^k lanes of a kernel's row count keep that
+// layout, which runs at the rate of its copy (512^3: 400 against 395 GDOF/s).
+// Others take the row count that divides them into at most 64 lanes, else the
+// one that leaves the fewest of a wavefront's rows idle (halo lanes and the
+// lanes beyond the last line count as idle).
+//
+// Strided lines (a workgroup holds the lanes of 8-32 pairs of adjacent lines):
+// the fewest rows per lane that keep a line within 32 lanes, so that 16 pairs
+// make 512 threads and two workgroups share a compute unit.  Lanes of one size
+// are preferred for r >= 2, whose windows are wide enough that most lanes of
+// a line of two sizes would read window rows of their own (tenth-order
+// derivative, n = 300 on ragged planes: 257 GDOF/s with 25 lanes of 12 rows,
+// 212 with 19 of 15 or 16).
+static void choose_windows(const cb_plan_desc &d, Plan &p) {
+  if (d.per_row || d.rows_per_lane || d.lines_per_wg || d.block_barriers || d.x_staging || d.interior) return;
+  if (d.precision != CB_FP64) return;
+  const int n = d.n, R = d.r;
+  const bool cyclic = d.cyclic != 0;
+  const int parts = d.partitions > 1 ? d.partitions : 0;
+  const double tol = std::ldexp(1.0, -57);
+  auto build = [&](int M, bool ring, WinLayout &w) { return build_window(n, R, d.bands, cyclic, M, tol, ring, w); };
+  if (cyclic && (parts || !(p.segs[0].uniform && n <= 2048))) {
+    static const int exact1[] = {12, 10, 16, 8, 20, 24}, exact2[] = {12, 16, 10, 20, 24, 8}, exact3[] = {16};
+    const int *exact = R == 1 ? exact1 : (R == 2 ? exact2 : exact3);
+    const int count = R == 3 ? 1 : 6;
+    for (int i = 0; i < count && !p.wx.M && !parts; ++i)
+      if (n % exact[i] == 0 && n / exact[i] <= 64) build(exact[i], false, p.wx);
+    double best = 0.0;
+    if (!p.wx.M)
+      for (int M : {16, 12, 10, 8, 20, 24}) {
+        WinLayout w;
+        if ((R == 1 && M > 16) || (R == 2 && M < 16) || (R == 3 && M != 16) || !build(M, true, w)) continue;
+        const int own = 64 - 2 * (w.D + 1), chunks = parts ? parts : (w.L + own - 1) / own;
+        const int lanes = (w.L + chunks - 1) / chunks + 2 * (w.D + 1);
+        if (lanes > 64 || n < (w.D + 2) * M + 4) continue;  // (a ring's window may wrap once)
+        const double busy = (double)n / chunks * (64 / lanes) / (64 * M) * (M == 16 ? 1.1 : 1.0);
+        if (busy > best) {
+          best = busy;
+          p.wx = w;
+        }
+      }
+  }
+  int order[3] = {16, 12, 8};
+  if (R == 1) {
+    order[0] = n <= 256 ? 8 : (n <= 384 ? 12 : 16);
+    order[1] = n <= 256 ? 12 : (n <= 384 ? 16 : 12);
+    order[2] = n <= 256 ? 16 : 8;
+  } else if (R == 2) {
+    if (n <= 64) std::swap(order[0], order[2]);
+    else if (n % 16 != 0 && n % 12 == 0 && n <= 384) std::swap(order[0], order[1]);
+  }
+  for (int M : order)
+    if ((R < 3 || M == 16) && !p.ws.M) build(M, false, p.ws);
+}
+
+cb_status build_plan(const cb_plan_desc &d, Plan &p, std::string &msg, bool windows) {
   if (d.r < 1 || d.r > kMaxR) {
     msg = "r must be 1 (tridiagonal), 2 (pentadiagonal) or 3 (heptadiagonal)";
     return d.r > kMaxR ? CB_ERR_UNSUPPORTED : CB_ERR_INVALID_ARG;
@@ -1043,12 +1104,13 @@ cb_status build_plan(const cb_plan_desc &d, Plan &p, std::string &msg) {
       dw.interior = 0;
       auto w = std::make_shared<Plan>();
       std::string m2;
-      if (build_plan(dw, *w, m2) == CB_OK) p.strided_wg = w;  // else strided lines stay whole
+      if (build_plan(dw, *w, m2, false) == CB_OK) p.strided_wg = w;  // else strided lines stay whole
     }
     if (d.lines_per_wg && d.lines_per_wg * p.L > 1024) {
       msg = "lines_per_wg * lanes exceeds 1024 threads";
       return CB_ERR_INVALID_ARG;
     }
+    if (windows) choose_windows(d, p);
     return CB_OK;
   }
   // P > 1: workgroup partitions, each with R interface rows and an interior
@@ -1170,7 +1232,9 @@ cb_status build_plan(const cb_plan_desc &d, Plan &p, std::string &msg) {
     }
   s = boundary_rows(P, R, p.wg_start, line_coef, p.Kw, p.bfun, msg);
   if (s != CB_OK) return s;
-  return wg_program(B, p.prog, msg);
+  s = wg_program(B, p.prog, msg);
+  if (s == CB_OK && windows) choose_windows(d, p);
+  return s;
 }
 
 }  // namespace cb

@@ -86,6 +86,41 @@ struct RedProgram {
   std::vector<std::vector<int>> detached;  // rows detached at each level
 };
 
+// ---------------------------------------------------------------------------
+// Windowed lanes: the layout of a constant-band line for the kernels of win.h.
+// The line's n rows are split over L lanes (any L) of base + 1 rows (the first
+// `extra` lanes) or base rows, M = the larger of the two; a lane's first R rows
+// are its interface rows, the rest its interior block D_l (Sec. 3).  All D_l
+// are leading blocks of one Toeplitz band, so elimination without pivoting has
+// the same factors D = L U for lanes of either size, and everything a row of a
+// lane needs is one table for the whole line:
+//   row[j]  k[R]     L[j][j-q]                                    (q = 1..R)
+//           v[R]     (U~_l U^{-1})[a][j]: first rows of y_l = U^{-1} z, folded
+//                    into the interface right-hand side of Eq. (21)
+//           ell[R]   (L^{-1} L_l)[j][c]: coupling to the own interface rows
+//           dinv     1 / U[j][j]
+//           u[R]     U[j][j+q] / U[j][j]
+//   z       L~ U_last^{-1} [2][R][R]: what a lane of base + 1 (0) or base (1)
+//           rows sends its successor, from its last R values of z = L^{-1} b
+// The reduced system of Eqs. (18)-(21) couples neighbouring lanes by factors
+// that decay with the rows between them, so its inverse is kept as a window:
+//   g       [rows][2D+1][R][R]: x~_l = sum_{|d| <= D} g[d] b^_{l+d}; the
+//           entries left out sum to at most 2^-57 of a row's absolute sum
+//           (2^-31 in FP32), below the rounding of the sum itself.  gidx[l] is
+//           lane l's row (lanes whose neighbourhood of sizes is alike share it).
+// ---------------------------------------------------------------------------
+struct WinLayout {
+  int M = 0, L = 0, base = 0, extra = 0, D = 0;  // M = 0: no such layout
+  int uniform = 0;                               // cyclic, every lane M rows: one g row
+  std::vector<double> coef;                      // row[M - R][4R + 1], then z
+  std::vector<double> g;
+  std::vector<int> gidx;
+  const void *d_coef = nullptr, *d_g = nullptr;  // double, or float in FP32 plans
+  const int *d_gidx = nullptr;
+};
+constexpr int win_row_size(int R) { return 4 * R + 1; }
+constexpr int kWinMaxD = 8;  // widest window the kernels take
+
 // Device view of a segment plan (POD, passed inside kernel arguments).
 struct SegDev {
   int S, L, M, Tint, Tred, uniform, m, block, ntypes, ilu;
@@ -153,10 +188,21 @@ struct Plan {
   // matrix split into workgroup partitions of about 512 rows, since a whole
   // line per workgroup would leave room for only a few adjacent lines
   std::shared_ptr<Plan> strided_wg;
+  WinLayout wx, ws;  // windowed lanes of unit-stride and of strided launches
   std::shared_ptr<ScratchCache> sc = std::make_shared<ScratchCache>();
 };
 
 // Builds the host-side factorisation.  Returns CB_OK or an error with msg.
-cb_status build_plan(const cb_plan_desc &d, Plan &p, std::string &msg);
+// windows: also the windowed lanes of plans that qualify.
+cb_status build_plan(const cb_plan_desc &d, Plan &p, std::string &msg, bool windows = true);
+
+// Windowed lanes of M rows for the n-row line with constant bands a_{-R..R};
+// false when the line has no such split, an elimination is not safely bounded
+// without pivoting or the window would exceed kWinMaxD lanes.  tol: share of a
+// window row's absolute sum that may be left out.  ring: M need not divide the
+// line, whose lanes all hold M rows and run on around its end (the last of
+// the ceil(n / M) lanes into rows of the first); a launch computes every lane
+// from a window of lanes that are all alike.
+bool build_window(int n, int R, const double *bands, bool cyclic, int M, double tol, bool ring, WinLayout &w);
 
 }  // namespace cb

@@ -1,0 +1,667 @@
+// Windowed-lane kernels: constant-band lines of any length whose inverse
+// decays (WinLayout in plan.h).  Included by the win_*.hip instance files.
+//
+// k_line's general layouts (line lengths that are no power of two times a
+// kernel's row count) were bound by latency: every lane read its coefficients
+// from LDS, log2 L exchanges ran one after the other, each behind a barrier,
+// and 112-127 VGPRs left four wavefronts per SIMD.  Here every row's
+// coefficients come through the scalar cache for lanes of any size, one
+// exchange solves the reduced system, and a lane's rows never leave their
+// registers, so what is left is memory: whole rows of 128-byte lines run at
+// 300-390 GDOF/s (4.8-6.2 TB/s), rows that share lines with their neighbours
+// at 230-310, where the requests to L2 are the limit (a 256-byte segment at an
+// odd offset takes three lines instead of two).  GDOF/s of the FP64 fused
+// derivative before -> after, x / y / z:
+//   500 x 613 x 338    sixth order  302 / 159 / 171 -> 371 / 306 / 297
+//   543 x 215 x 958    tenth order  104 / 149 / 121 -> 310 / 272 / 250
+// and of the solve of 2500 x 115 x 115 lines along x, sixth order 199 -> 345,
+// tenth order 94 -> 326 (chunks of lanes that recompute D + 1 lanes of their
+// neighbours instead of three launches that pass them through memory).
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "device.h"
+#include "launch.h"
+
+namespace cb {
+
+// Strided rows are read and written as pairs of adjacent lines, one pair per
+// thread: 16 bytes per access, coefficients fetched once for both lines, two
+// chains of dependent operations in flight (16 rows of two lines instead of 32
+// of one, 512^3 sixth order y / z 341 / 324 -> 355 / 348 GDOF/s).  Unit-stride
+// rows one line per thread.
+typedef float flt2 __attribute__((ext_vector_type(2)));
+typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));  // any 8-byte address
+template <typename T, int NL> struct WinVec { typedef T type; };
+template <> struct WinVec<double, 2> { typedef dbl2 type; };
+template <> struct WinVec<float, 2> { typedef flt2 type; };
+__device__ __forceinline__ void win_cast(double v, float &o) { o = (float)v; }
+__device__ __forceinline__ void win_cast(float v, double &o) { o = (double)v; }
+__device__ __forceinline__ void win_cast(dbl2 v, flt2 &o) { o = __builtin_convertvector(v, flt2); }
+__device__ __forceinline__ void win_cast(flt2 v, dbl2 &o) { o = __builtin_convertvector(v, dbl2); }
+
+constexpr int win_lines(int mode) { return mode == MODE_S ? 2 : 1; }  // lines per thread
+
+// LDS planes, one value per thread and plane: the halo of Q rows per side that
+// strided rows exchange for the stencil, or of R rows for the residual, and
+// what a lane shares for the reduced system (2R).  Where both together would
+// leave one workgroup to a compute unit, the second takes the first's place
+// behind a barrier of its own.
+constexpr int win_halo_planes(int R, int Q, bool ref, int mode) {
+  const int q = mode == MODE_S ? 2 * Q : 0, r = ref ? 2 * R : 0;
+  return q > r ? q : r;
+}
+constexpr bool win_shared_planes(int R, int Q, bool ref, int mode) {
+  return mode == MODE_S && win_halo_planes(R, Q, ref, mode) + 2 * R >= 8;
+}
+constexpr int win_planes(int R, int Q, bool ref, int mode) {
+  const int h = win_halo_planes(R, Q, ref, mode);
+  return win_shared_planes(R, Q, ref, mode) ? (h > 2 * R ? h : 2 * R) : h + 2 * R;
+}
+
+// Position of a thread: lane l of the Lw its line (or pair of lines) has in the
+// workgroup.  A plane holds, per line, the lanes' values between D + 1 spare
+// ones on either side: of a line that is whole the far lanes' again, so that
+// neighbours lie at a fixed distance (step) without a wrap; of a chunk nothing
+// that a stored lane depends on.
+struct WinPos {
+  int l, Lw, D, at, step, NS;  // at: the lane's slot; NS: slots per plane
+  bool live, whole, block;
+  __device__ __forceinline__ void sync() const {
+    if (block) {
+      __syncthreads();
+    } else {  // a line's lanes lie in one wavefront, whose LDS traffic is in order
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+  }
+  // share CNT values with the lanes up to `reach` away
+  template <int CNT, typename V>
+  __device__ __forceinline__ void publish(V *ex, const V (&v)[CNT], int reach) const {
+    if (live) {
+#pragma unroll
+      for (int i = 0; i < CNT; ++i) ex[i * NS + at] = v[i];
+      if (whole && l < reach) {
+#pragma unroll
+        for (int i = 0; i < CNT; ++i) ex[i * NS + at + Lw * step] = v[i];
+      }
+      if (whole && l >= Lw - reach) {
+#pragma unroll
+        for (int i = 0; i < CNT; ++i) ex[i * NS + at - Lw * step] = v[i];
+      }
+    }
+    sync();
+  }
+};
+
+// x~_l = sum_{|d| <= D} g[d] (c_{l+d} - t_{l+d-1}), the lane's window of the
+// reduced system's inverse, and x~_{l+1} by the same window one lane on (a
+// second exchange would cost a barrier).  ct: c and t of Eq. (21).  g: one row
+// for the whole wavefront, read through the scalar cache ahead of the barrier.
+template <int R, int D, typename T, typename V>
+__device__ __forceinline__ void win_reduce(const T *g, const WinPos &p, V *ex, const V (&ct)[2 * R], V (&xt)[R],
+                                           V (&xn)[R]) {
+  T gm[(2 * D + 1) * R * R];
+#pragma unroll
+  for (int i = 0; i < (2 * D + 1) * R * R; ++i) gm[i] = cld(g + i);
+  p.publish(ex, ct, D + 1);
+#pragma unroll
+  for (int a = 0; a < R; ++a) xt[a] = xn[a] = (V)(T)0;
+#pragma unroll
+  for (int d = -D; d <= D + 1; ++d) {
+#pragma unroll
+    for (int b = 0; b < R; ++b) {
+      const V v = ex[b * p.NS + p.at + d * p.step] - ex[(R + b) * p.NS + p.at + (d - 1) * p.step];
+#pragma unroll
+      for (int a = 0; a < R; ++a) {
+        if (d <= D) xt[a] += gm[(d <= D ? d + D : 0) * R * R + a * R + b] * v;
+        if (d > -D) xn[a] += gm[(d > -D ? d - 1 + D : 0) * R * R + a * R + b] * v;
+      }
+    }
+    // (a few reads in flight at a time: the lane's rows fill the registers)
+    if (R > 1 || (d + D) % 2) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+// The same for lanes that read different rows (gn: the next lane's), and for
+// wide windows.  g, gn: in LDS, or uniform.
+template <int R, typename T, typename V>
+__device__ __forceinline__ void win_reduce_any(const T *g, const T *gn, const WinPos &p, V *ex,
+                                               const V (&ct)[2 * R], V (&xt)[R], V (&xn)[R]) {
+  p.publish(ex, ct, p.D + 1);
+#pragma unroll
+  for (int a = 0; a < R; ++a) xt[a] = xn[a] = (V)(T)0;
+  const int at = p.at - p.D * p.step;
+  auto value = [&](int d, int b) { return ex[b * p.NS + at + d * p.step] - ex[(R + b) * p.NS + at + (d - 1) * p.step]; };
+  auto add = [&](V(&x)[R], const T *row, V v, int b) {
+#pragma unroll
+    for (int a = 0; a < R; ++a) x[a] += row[a * R + b] * v;
+  };
+#pragma unroll
+  for (int b = 0; b < R; ++b) add(xt, g, value(0, b), b);
+#pragma unroll 1
+  for (int d = 1; d <= 2 * p.D; ++d)
+#pragma unroll
+    for (int b = 0; b < R; ++b) {
+      const V v = value(d, b);
+      add(xt, g + d * R * R, v, b);
+      add(xn, gn + (d - 1) * R * R, v, b);
+    }
+#pragma unroll
+  for (int b = 0; b < R; ++b) add(xn, gn + 2 * p.D * R * R, value(2 * p.D + 1, b), b);
+}
+
+// Solve the lane's rows v (b on entry, x on exit).  sh: the lane holds M - 1
+// rows.  last: the last lane of an acyclic line.  gi, gin: the lane's and the
+// next lane's row of the window table g, whose copy in LDS is gl.
+template <int R, int M, typename T, typename V, bool UNI>
+__device__ __forceinline__ void win_solve(V (&v)[M], const T *cf, const T *g, const T *gl, int gi, int gin, const WinPos &p, V *ex,
+                                          bool sh, bool last) {
+  constexpr int N = M - R, RW = win_row_size(R), RR = R * R;
+  const int D = p.D;
+  const V zero = (V)(T)0;
+  // z = L^{-1} b on the interior rows
+#pragma unroll
+  for (int j = 1; j < N; ++j)
+#pragma unroll
+    for (int q = 1; q <= R; ++q)
+      if (j - q >= 0) v[R + j] -= cld(cf + j * RW + q - 1) * v[R + j - q];
+  if (!UNI) v[M - 1] = sh ? zero : v[M - 1];
+  // c = b~ - U~ y_first, t = L~ y_last (Eq. (21))
+  V ct[2 * R], xt[R], xn[R + 1], xr[R];
+#pragma unroll
+  for (int a = 0; a < R; ++a) {
+    V acc = v[a];
+#pragma unroll
+    for (int j = 0; j < N; ++j) acc -= cld(cf + j * RW + R + a) * v[R + j];
+    ct[a] = acc;
+  }
+  {
+    V zl[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) zl[i] = UNI ? v[M - R + i] : (sh ? v[M - R - 1 + i] : v[M - R + i]);
+#pragma unroll
+    for (int a = 0; a < R; ++a) {
+      V acc = zero;
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const T z0 = cld(cf + N * RW + a * R + i);
+        acc += (UNI ? z0 : (sh ? cld(cf + N * RW + RR + a * R + i) : z0)) * zl[i];
+      }
+      ct[R + a] = (!UNI && last) ? zero : acc;
+    }
+  }
+  // x~: most wavefronts hold lanes that share one window row
+  const int gu = UNI ? 0 : __builtin_amdgcn_readfirstlane(gi);
+  const T *gw = g + (size_t)gu * ((2 * D + 1) * RR);
+  constexpr int DF = M >= 24 ? 3 : (R == 1 ? 6 : 4);  // unrolled windows
+  if (D <= DF && (UNI || __all(gi == gu && gin == gu))) {
+    if (D == 1) win_reduce<R, 1, T, V>(gw, p, ex, ct, xt, xr);
+    else if (D == 2) win_reduce<R, 2, T, V>(gw, p, ex, ct, xt, xr);
+    else if (D == 3) win_reduce<R, 3, T, V>(gw, p, ex, ct, xt, xr);
+    else if (DF >= 4 && D == 4) win_reduce<R, DF >= 4 ? 4 : 1, T, V>(gw, p, ex, ct, xt, xr);
+    else if (DF >= 5 && D == 5) win_reduce<R, DF >= 5 ? 5 : 1, T, V>(gw, p, ex, ct, xt, xr);
+    else if (DF >= 6) win_reduce<R, DF >= 6 ? 6 : 1, T, V>(gw, p, ex, ct, xt, xr);
+  } else {
+    const T *gs = UNI ? g : gl;
+    win_reduce_any<R, T, V>(gs + gi * ((2 * D + 1) * RR), gs + gin * ((2 * D + 1) * RR), p, ex, ct, xt, xr);
+  }
+#pragma unroll
+  for (int a = 0; a < R; ++a) xn[a] = (!UNI && last) ? zero : xr[a];
+  xn[R] = zero;
+  // x = U^{-1} (z - ell x~_l), with the next lane's interface rows beyond its end
+  V e[R];  // slots M .. M+R-1
+#pragma unroll
+  for (int a = 0; a < R; ++a) e[a] = UNI ? xn[a] : (sh ? xn[a + 1] : xn[a]);
+#pragma unroll
+  for (int j = N - 1; j >= 0; --j) {
+    V acc = v[R + j];
+#pragma unroll
+    for (int a = 0; a < R; ++a) acc -= cld(cf + j * RW + 2 * R + a) * xt[a];
+    acc *= cld(cf + j * RW + 3 * R);
+#pragma unroll
+    for (int q = 1; q <= R; ++q)
+      acc -= cld(cf + j * RW + 3 * R + q) * (j + q < N ? v[j + q < N ? R + j + q : 0] : e[j + q < N ? 0 : j + q - N]);
+    v[R + j] = (!UNI && j == N - 1) ? (sh ? xn[0] : acc) : acc;
+  }
+#pragma unroll
+  for (int a = 0; a < R; ++a) v[a] = xt[a];
+}
+
+// v[k] of a lane whose rows before its first are prev[Q] and whose slots from
+// M - 1 on are tail[Q + 1] (tail[0]: row M - 1, or the next lane's first row
+// when the lane holds M - 1 rows).
+template <int Q, int M, typename V>
+__device__ __forceinline__ V win_at(const V (&v)[M], const V (&prev)[Q], const V (&tail)[Q + 1], int k) {
+  if (k < 0) return prev[k + Q < 0 ? 0 : k + Q];
+  if (k < M - 1) return v[k < M - 1 ? k : 0];
+  return tail[k - M + 1 > Q ? Q : (k < M - 1 ? 0 : k - M + 1)];
+}
+template <int Q, int M, bool UNI, typename V>
+__device__ __forceinline__ void win_tail(const V (&v)[M], const V (&next)[Q], bool sh, V (&tail)[Q + 1]) {
+  tail[0] = UNI ? v[M - 1] : (sh ? next[0] : v[M - 1]);
+#pragma unroll
+  for (int i = 0; i < Q; ++i) tail[1 + i] = UNI ? next[i] : (sh ? next[i + 1 < Q ? i + 1 : i] : next[i]);
+}
+
+// Exchange of the Q rows at either end of every lane.
+template <int Q, int M, bool UNI, typename V>
+__device__ __forceinline__ void win_halo(const V (&v)[M], bool sh, const WinPos &p, V *ex, V (&prev)[Q], V (&next)[Q]) {
+  V h[2 * Q];
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    h[i] = v[i];
+    h[Q + i] = UNI ? v[M - Q + i] : (sh ? v[M - 1 - Q + i] : v[M - Q + i]);
+  }
+  p.publish(ex, h, 1);
+#pragma unroll
+  for (int i = 0; i < Q; ++i) {
+    prev[i] = ex[(Q + i) * p.NS + p.at - p.step];
+    next[i] = ex[i * p.NS + p.at + p.step];
+  }
+}
+
+// A row of a pair of adjacent lines; one: only the first line exists.
+template <bool NT>
+__device__ __forceinline__ dbl2 win_load2(const double *q, bool one) {
+  if (one) return dbl2{*q, 0.0};
+  const dbl2u *s = reinterpret_cast<const dbl2u *>(q);
+  return NT ? (dbl2)__builtin_nontemporal_load(s) : (dbl2)*s;
+}
+
+template <bool NT>
+__device__ __forceinline__ void win_store2(dbl2 v, double *q) {
+  dbl2u *s = reinterpret_cast<dbl2u *>(q);
+  if (NT) __builtin_nontemporal_store((dbl2u)v, s);
+  else *s = v;
+}
+template <bool B> struct WinFlag { static constexpr bool value = B; };
+
+// One tile: the lanes of W lines (pairs of lines), or of one run of lanes
+// (chunk) of each of them with H halo lanes on either side.
+template <int R, int M, typename T, bool REF, int MODE, int Q, bool UNI, bool COPY>
+__device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double *smem) {
+  constexpr int QQ = Q > 0 ? Q : 1;
+  constexpr int KT = Q > 0 ? M + 2 : M;  // tile rows a lane loads (a window's halo needs one or two more)
+  typedef typename WinVec<double, win_lines(MODE)>::type VD;
+  typedef typename WinVec<T, win_lines(MODE)>::type V;
+  const int tid = threadIdx.x;
+  WinPos p;
+  p.Lw = a.Lw;
+  p.D = a.D;
+  p.block = MODE == MODE_S;
+  p.whole = a.H == 0;
+  int li;
+  if (MODE == MODE_S) {
+    p.l = tid >> a.lgW;
+    li = tid & ((1 << a.lgW) - 1);
+    p.live = p.l < a.Lw;
+    p.step = 1 << a.lgW;
+    p.NS = (a.Lw + 2 * a.D + 2) << a.lgW;
+    p.l = p.live ? p.l : 0;
+    p.at = ((p.l + a.D + 1) << a.lgW) + li;
+  } else {
+    const int t = tid & 63;
+    const int q = (int)(((uint32_t)t * a.linv) >> 16);  // t / Lw
+    p.live = q < a.lpw;
+    p.l = p.live ? t - q * a.Lw : 0;
+    li = (tid >> 6) * a.lpw + (p.live ? q : 0);
+    p.step = 1;
+    p.NS = a.W * (a.Lw + 2 * a.D + 2);
+    p.at = li * (a.Lw + 2 * a.D + 2) + a.D + 1 + p.l;
+  }
+  const bool live = p.live;
+  uint32_t ch = 0, lt = tile;
+  if (a.nch > 1) {
+    if (a.chunk_fast) {
+      lt = tile / (uint32_t)a.nch;
+      ch = tile - lt * (uint32_t)a.nch;
+    } else {
+      ch = tile / a.ltiles;
+      lt = tile - ch * a.ltiles;
+    }
+  }
+  const int64_t line = (int64_t)lt * a.W + li;
+  const bool lactive = live && line < a.nlines;
+  const FastDiv fd{a.nudiv.d, a.nudiv.mul, a.nudiv.s1, a.nudiv.s2};
+  const uint32_t line32 = lactive ? (uint32_t)line : 0u;
+  const uint32_t lv = fd.div(line32), lu = line32 - lv * a.nudiv.d;
+  const int64_t lbase = (int64_t)lu * a.su + (int64_t)lv * a.sv;
+  const bool one = MODE == MODE_S && (int)lu == a.one;  // a pair with only its first line
+  // the lane: g of the line's L lanes; own: lanes this tile stores, between H
+  // halo lanes on either side
+  const int H = a.H;
+  int own = a.L - (int)ch * a.Lc;
+  own = own < a.Lc ? own : a.Lc;
+  int g = (int)ch * a.Lc - H + p.l;
+  bool active = lactive && p.l < own + 2 * H;
+  const bool store = active && p.l >= H && p.l < H + own;
+  bool sh = false;
+  int m = M, start = 0;
+  if (MODE == MODE_S) {
+    if (a.acyclic) active = active && g >= 0 && g < a.L;
+    g = g < 0 ? g + a.L : (g >= a.L ? g - a.L : g);
+    g = g < 0 || g >= a.L ? 0 : g;  // (lanes past the last chunk's window)
+    sh = !UNI && g >= a.extra && a.extra > 0;
+    m = sh ? M - 1 : M;
+    start = UNI ? g * M : g * a.base + (g < a.extra ? g : a.extra);
+  }
+  VD b64[M];
+  VD gp[QQ], gn[QQ];
+  const VD zero = (VD)0.0;
+  // unit-stride lines go through an LDS tile: word e holds row r0 + e (modulo n)
+  double *tb = nullptr;
+  const double *lin = a.in + lbase;
+  int r0 = 0, len = 0;
+  // (a pad word per M words: lane l's rows are words l (M + 1) + 0..M-1, free of
+  // bank conflicts; halo rows before lane 0 have negative e, words -1 - |e|)
+  auto at = [](int e) { return e + (int)((uint32_t)(e + M) / (uint32_t)M) - 1; };
+  constexpr int QP = (Q + 1) & ~1;  // halo rows beyond the window's lanes, kept even
+  if constexpr (MODE == MODE_X) {
+    tb = smem + (size_t)win_planes(R, Q, REF, MODE) * p.NS + (size_t)li * a.pitch + QP + 2;
+    len = a.n;
+    if (H > 0) {
+      r0 = ((int)ch * a.Lc - H) * M;
+      len = (own + 2 * H) * M;
+    }
+    const int e0 = H > 0 ? -QP : 0, e1 = H > 0 ? len + QP : len;
+    // pairs of rows from any 8-byte address (r0, len and QP are even); the ring
+    // wraps between the rows of a pair when n is odd
+    auto load = [&](auto nt) {
+      dbl2 t2[KT / 2];
+#pragma unroll
+      for (int k = 0; k < KT / 2; ++k) {
+        const int e = e0 + 2 * (p.l + k * a.Lw);
+        int r = r0 + e;
+        r = r < 0 ? r + a.n : (r >= a.n ? r - a.n : r);
+        t2[k] = dbl2{0.0, 0.0};
+        if (lactive && e < e1) {
+          if (r == a.n - 1) t2[k] = dbl2{lin[r], lin[0]};
+          else t2[k] = win_load2<decltype(nt)::value>(lin + r, false);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < KT / 2; ++k) {
+        const int e = e0 + 2 * (p.l + k * a.Lw);
+        if (live && e < e1) {
+          const int w = at(e);
+          tb[w] = t2[k].x;
+          tb[w + 1] = t2[k].y;
+        }
+      }
+    };
+    if (a.nt) load(WinFlag<true>());
+    else load(WinFlag<false>());
+    p.sync();
+#pragma unroll
+    for (int k = 0; k < M; ++k) b64[k] = active ? tb[p.l * (M + 1) + k] : 0.0;
+  } else {
+    const double *in = lin + (int64_t)start * a.rs;
+    if (a.nt && !one) {
+#pragma unroll
+      for (int k = 0; k < M; ++k)
+        b64[k] = (active && (UNI || k < M - 1 || !sh)) ? win_load2<true>(in + k * a.rs, false) : zero;
+    } else if (!one) {
+#pragma unroll
+      for (int k = 0; k < M; ++k)
+        b64[k] = (active && (UNI || k < M - 1 || !sh)) ? win_load2<false>(in + k * a.rs, false) : zero;
+    } else {
+#pragma unroll
+      for (int k = 0; k < M; ++k)
+        b64[k] = (active && (UNI || k < M - 1 || !sh)) ? win_load2<false>(in + k * a.rs, true) : zero;
+    }
+    if (Q > 0 && !COPY) {
+      // the window's ends take their halo from memory
+#pragma unroll
+      for (int i = 0; i < QQ; ++i) {
+        gp[i] = gn[i] = zero;
+        if (H > 0 && active && p.l == 0) {
+          const int r = start - Q + i;
+          gp[i] = win_load2<false>(lin + (int64_t)(r < 0 ? r + a.n : r) * a.rs, one);
+        }
+        if (H > 0 && active && p.l == own + 2 * H - 1) {
+          const int r = start + m + i;
+          gn[i] = win_load2<false>(lin + (int64_t)(r >= a.n ? r - a.n : r) * a.rs, one);
+        }
+      }
+    }
+  }
+  // lanes of two sizes read different rows of the window table: copied to LDS
+  // (visible after the next exchange)
+  T *gl = reinterpret_cast<T *>(smem + (size_t)win_planes(R, Q, REF, MODE) * win_lines(MODE) * p.NS);
+  if (!UNI && !COPY) {
+    const T *gw = static_cast<const T *>(a.g);
+    for (int i = tid; i < a.gcount; i += blockDim.x) gl[i] = gw[i];
+  }
+  if (Q > 0 && !COPY) {  // fused right-hand-side stencil (Eqs. (1)-(2)), periodic
+    VD fp[QQ], fn[QQ], tail[QQ + 1];
+    if constexpr (MODE == MODE_X) {
+#pragma unroll
+      for (int i = 0; i < QQ; ++i) {
+        // the last rows of the lane before and the first of the next one
+        int e = p.l * (M + 1) - 1 - Q + i, f = (p.l + 1) * (M + 1) + i;
+        if (p.l == 0 && H == 0) e = a.Lw * (M + 1) - 1 - Q + i;
+        if (p.l == a.Lw - 1 && H == 0) f = i;
+        fp[i] = active ? tb[e] : 0.0;
+        fn[i] = active ? tb[f] : 0.0;
+      }
+    } else {
+      win_halo<QQ, M, UNI, VD>(b64, sh, p, reinterpret_cast<VD *>(smem), fp, fn);
+      if (H > 0) {
+#pragma unroll
+        for (int i = 0; i < QQ; ++i) {
+          fp[i] = p.l == 0 ? gp[i] : fp[i];
+          fn[i] = p.l == own + 2 * H - 1 ? gn[i] : fn[i];
+        }
+      }
+    }
+    win_tail<QQ, M, UNI, VD>(b64, fn, sh, tail);
+    VD bb[M];
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+      VD acc = zero;
+#pragma unroll
+      for (int q = -Q; q <= Q; ++q) acc += a.stc[q + 3] * win_at<QQ, M, VD>(b64, fp, tail, k + q);
+      bb[k] = (!UNI && k == M - 1 && sh) ? zero : acc;
+    }
+#pragma unroll
+    for (int k = 0; k < M; ++k) b64[k] = bb[k];
+  }
+  if (!COPY) {
+    const T *cf = static_cast<const T *>(a.coef);
+    const T *gw = static_cast<const T *>(a.g);
+    const int gi = UNI ? 0 : a.gidx[g], gin = UNI ? 0 : a.gidx[g + 1 < a.L ? g + 1 : 0];
+    const bool last = !UNI && a.acyclic && g == a.L - 1;
+    constexpr bool shared = win_shared_planes(R, Q, REF, MODE);
+    constexpr int HP = win_halo_planes(R, Q, REF, MODE) * win_lines(MODE);
+    V *ex = reinterpret_cast<V *>(smem + (shared ? 0 : (size_t)HP * p.NS));
+    auto solve = [&](V(&v)[M], bool halo) {
+      if (shared && halo) p.sync();  // the halo has been read
+      win_solve<R, M, T, V, UNI>(v, cf, gw, gl, gi, gin, p, ex, sh, last);
+    };
+    if constexpr (sizeof(T) == 8) {
+      solve(b64, Q > 0);
+    } else if constexpr (!REF) {
+      V v[M];
+#pragma unroll
+      for (int k = 0; k < M; ++k) win_cast(b64[k], v[k]);
+      solve(v, Q > 0);
+#pragma unroll
+      for (int k = 0; k < M; ++k) win_cast(v[k], b64[k]);
+    } else {
+      // FP32 reduction with FP64 residual refinement: x <- x + A32^{-1}(b - A x)
+      const bool first = a.acyclic && g == 0;
+      double x64[M];
+      V v[M];
+#pragma unroll
+      for (int k = 0; k < M; ++k) win_cast(b64[k], v[k]);
+      solve(v, Q > 0);
+#pragma unroll
+      for (int k = 0; k < M; ++k) win_cast(v[k], x64[k]);
+      for (int it = 0; it < a.refine_iters; ++it) {
+        VD xp[R], xn[R], tail[R + 1];
+        if (shared) p.sync();  // the window has been read
+        win_halo<R, M, UNI, VD>(x64, sh, p, reinterpret_cast<VD *>(smem), xp, xn);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          xp[i] = first ? zero : xp[i];
+          xn[i] = last ? zero : xn[i];
+        }
+        win_tail<R, M, UNI, VD>(x64, xn, sh, tail);
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+          VD r = b64[k];
+#pragma unroll
+          for (int o = -R; o <= R; ++o) r -= a.bands[o + R] * win_at<R, M, VD>(x64, xp, tail, k + o);
+          win_cast((!UNI && k == M - 1 && sh) ? zero : r, v[k]);
+        }
+        solve(v, true);
+#pragma unroll
+        for (int k = 0; k < M; ++k) {
+          VD d;
+          win_cast(v[k], d);
+          x64[k] += d;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < M; ++k) b64[k] = x64[k];
+    }
+  }
+  if constexpr (MODE == MODE_X) {
+    if (COPY) p.sync();
+#pragma unroll
+    for (int k = 0; k < M; ++k)
+      if (active) tb[p.l * (M + 1) + k] = b64[k];
+    p.sync();
+    double *lout = a.out + lbase;
+    int s0 = 0, s1 = len;  // tile words this tile stores
+    if (H > 0) {
+      s0 = H * M;
+      const int rows = a.n - (int)ch * a.Lc * M;
+      s1 = s0 + (rows < own * M ? rows : own * M);
+    }
+    auto put = [&](auto nt) {
+#pragma unroll
+      for (int k = 0; k < KT / 2; ++k) {
+        const int e = 2 * (p.l + k * a.Lw);
+        if (lactive && e >= s0 && e < s1) {
+          double *q = lout + r0 + e;
+          const int w = at(e);
+          if (e + 1 == s1) *q = tb[w];
+          else win_store2<decltype(nt)::value>(dbl2{tb[w], tb[w + 1]}, q);
+        }
+      }
+    };
+    if (a.nt) put(WinFlag<true>());
+    else put(WinFlag<false>());
+  } else {
+    if (!store) return;
+    // (the output row as a distance from the input row: one address stays live)
+    double *out = const_cast<double *>(lin) + (a.out - a.in) + (int64_t)start * a.rs;
+    if (a.nt && !one) {
+#pragma unroll
+      for (int k = 0; k < M; ++k)
+        if (UNI || k < M - 1 || !sh) win_store2<true>(b64[k], out + k * a.rs);
+    } else if (!one) {
+#pragma unroll
+      for (int k = 0; k < M; ++k)
+        if (UNI || k < M - 1 || !sh) win_store2<false>(b64[k], out + k * a.rs);
+    } else {
+#pragma unroll
+      for (int k = 0; k < M; ++k)
+        if (UNI || k < M - 1 || !sh) out[k * a.rs] = b64[k].x;
+    }
+  }
+}
+
+// Workgroup bound of an instance: unit-stride ones run 256 threads.
+template <int MODE>
+constexpr int win_max_threads() {
+  return MODE == MODE_X ? 256 : 1024;
+}
+
+template <int R, int M, typename T, bool REF, int MODE, int Q, bool UNI, bool COPY = false>
+__global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win(const WinArgs a) {
+  extern __shared__ __align__(16) double smem[];
+  uint32_t tile = blockIdx.x;
+  if (a.xcds > 1) {  // tiles grouped by XCD, as in k_line
+    const uint32_t X = (uint32_t)a.xcds, G = gridDim.x, q = G / X, rem = G % X;
+    const uint32_t j = tile % X, s = tile / X;
+    tile = j * q + (j < rem ? j : rem) + s;
+  }
+  win_tile<R, M, T, REF, MODE, Q, UNI, COPY>(a, tile, smem);
+}
+
+// Batched launch over the tiles of many items of one instance, as k_batched.
+// Wavefronts beyond an item's own workgroup size leave at once (a barrier
+// counts the wavefronts that remain) or, in the persistent form, idle.
+template <int R, int M, typename T, bool REF, int MODE, int Q, bool UNI>
+__global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win_batched(BatchHdr *hdr,
+                                                                             const WinItemDev *__restrict__ items,
+                                                                             int per_tile) {
+  extern __shared__ __align__(16) double smem[];
+  const int64_t total = hdr->total_tiles;
+  const int nitems = hdr->n_items;
+  auto item_of = [&](int64_t t) {
+    int lo = 0, hi = nitems - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (items[mid].tile_begin <= t) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+  };
+  if (per_tile) {
+    const int64_t t = blockIdx.x;
+    if (t >= total) return;
+    const int i = item_of(t);
+    const WinItemDev &it = items[i];
+    if ((int)threadIdx.x >= it.threads) return;
+    uint32_t local = (uint32_t)(t - it.tile_begin);
+    if (it.a.xcds > 1) {
+      const uint32_t G = (uint32_t)((i + 1 < nitems ? items[i + 1].tile_begin : total) - it.tile_begin);
+      const uint32_t X = (uint32_t)it.a.xcds, q = G / X, rem = G % X, j = local % X, s = local / X;
+      local = j * q + (j < rem ? j : rem) + s;
+    }
+    win_tile<R, M, T, REF, MODE, Q, UNI, false>(it.a, local, smem);
+    return;
+  }
+  for (;;) {
+    unsigned long long *next = reinterpret_cast<unsigned long long *>(smem);
+    if (threadIdx.x == 0) *next = atomicAdd(&hdr->next_tile, 1ull);
+    __syncthreads();
+    const int64_t t = (int64_t)*next;
+    __syncthreads();
+    if (t >= total) break;
+    const WinItemDev &it = items[item_of(t)];
+    win_tile<R, M, T, REF, MODE, Q, UNI, false>(it.a, (uint32_t)(t - it.tile_begin), smem);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    __threadfence();
+    const unsigned prev = atomicAdd(&hdr->done, 1u);
+    if (prev == gridDim.x - 1) {
+      atomicExch(&hdr->next_tile, 0ull);
+      atomicExch(&hdr->done, 0u);
+      __threadfence();
+    }
+  }
+}
+
+template <int R, int M, typename T, bool REF, int MODE, int Q, bool UNI>
+const void *win_batched() {
+  if constexpr (Q > 0) return (const void *)&k_win_batched<R, M, T, REF, MODE, Q, UNI>;
+  else return nullptr;
+}
+
+#define CB_WIN_INST(R, M, T, REF, MODE, Q, UNI)                                                     \
+  {R, M, sizeof(T) == 8 ? 0 : (REF ? 2 : 1), MODE, Q, UNI, win_max_threads<MODE>(),                  \
+   win_planes(R, Q, REF, MODE) * win_lines(MODE), (const void *)&k_win<R, M, T, REF, MODE, Q, UNI>, \
+   win_batched<R, M, T, REF, MODE, Q, UNI>()}
+#define CB_WIN_U(R, M, T, REF, MODE, U) \
+  CB_WIN_INST(R, M, T, REF, MODE, 0, U), CB_WIN_INST(R, M, T, REF, MODE, 2, U), CB_WIN_INST(R, M, T, REF, MODE, 3, U)
+#define CB_WIN_X(R, M, T, REF) CB_WIN_U(R, M, T, REF, MODE_X, true)
+#define CB_WIN_S(R, M, T, REF) CB_WIN_U(R, M, T, REF, MODE_S, false), CB_WIN_U(R, M, T, REF, MODE_S, true)
+
+}  // namespace cb

@@ -1,0 +1,359 @@
+// Host factorisation of windowed lanes (WinLayout in plan.h): one elimination
+// of the Toeplitz band for every lane's interior block, and the windows of the
+// reduced system's inverse (Sec. 3-4 with lanes as partitions).  Part of
+// plan.cpp.
+#pragma once
+#include <algorithm>
+#include <cmath>
+#include <map>
+
+#include "plan.h"
+
+namespace cb {
+namespace window {
+
+struct Blk {  // R x R, row-major
+  double v[kMaxR * kMaxR] = {};
+};
+
+Blk mul(const Blk &a, const Blk &b, int R) {
+  Blk c;
+  for (int i = 0; i < R; ++i)
+    for (int k = 0; k < R; ++k)
+      for (int j = 0; j < R; ++j) c.v[i * R + j] += a.v[i * R + k] * b.v[k * R + j];
+  return c;
+}
+Blk sub(const Blk &a, const Blk &b, int R) {
+  Blk c;
+  for (int i = 0; i < R * R; ++i) c.v[i] = a.v[i] - b.v[i];
+  return c;
+}
+Blk neg(const Blk &a, int R) {
+  Blk c;
+  for (int i = 0; i < R * R; ++i) c.v[i] = -a.v[i];
+  return c;
+}
+double abs_sum(const Blk &a, int R) {
+  double s = 0.0;
+  for (int i = 0; i < R * R; ++i) s += std::fabs(a.v[i]);
+  return s;
+}
+
+// m x m inverse by Gauss-Jordan with partial pivoting; false when a pivot is
+// below 1e-10 of the largest entry.
+bool invert(int m, const double *a, double *out) {
+  std::vector<double> t(a, a + (size_t)m * m);
+  double amax = 0.0;
+  for (double v : t) amax = std::max(amax, std::fabs(v));
+  if (!(amax > 0.0) || !std::isfinite(amax)) return false;
+  for (int i = 0; i < m * m; ++i) out[i] = 0.0;
+  for (int i = 0; i < m; ++i) out[i * m + i] = 1.0;
+  for (int k = 0; k < m; ++k) {
+    int p = k;
+    for (int i = k + 1; i < m; ++i)
+      if (std::fabs(t[i * m + k]) > std::fabs(t[p * m + k])) p = i;
+    if (!(std::fabs(t[p * m + k]) > 1e-10 * amax)) return false;
+    if (p != k)
+      for (int j = 0; j < m; ++j) {
+        std::swap(t[k * m + j], t[p * m + j]);
+        std::swap(out[k * m + j], out[p * m + j]);
+      }
+    const double d = 1.0 / t[k * m + k];
+    for (int j = 0; j < m; ++j) {
+      t[k * m + j] *= d;
+      out[k * m + j] *= d;
+    }
+    for (int i = 0; i < m; ++i) {
+      const double f = t[i * m + k];
+      if (i == k || f == 0.0) continue;
+      for (int j = 0; j < m; ++j) {
+        t[i * m + j] -= f * t[k * m + j];
+        out[i * m + j] -= f * out[k * m + j];
+      }
+    }
+  }
+  return true;
+}
+bool invert(const Blk &a, int R, Blk &out) { return invert(R, a.v, out.v); }
+
+// The reduced system (Eqs. (18)-(20)) of one line: blocks of lane l from the
+// sizes of l and its predecessor (0: base + 1 rows, 1: base rows).
+struct Reduced {
+  int R = 1, L = 0, extra = 0;
+  bool cyclic = true;
+  Blk Lt, Ut, Dt;
+  Blk Sl[2], Rl[2], Sf[2], Rf[2];  // last and first R rows of D^{-1}L and D^{-1}U
+  int type(int l) const { return extra > 0 && l < extra ? 0 : 1; }
+  int wrap(int l) const { return l < 0 ? l + L : (l >= L ? l - L : l); }
+  Blk lower(int l) const {
+    if (!cyclic && l == 0) return Blk();
+    return neg(mul(Lt, Sl[type(wrap(l - 1))], R), R);
+  }
+  Blk upper(int l) const {
+    if (!cyclic && l == L - 1) return Blk();
+    return neg(mul(Ut, Rf[type(l)], R), R);
+  }
+  Blk diag(int l) const {
+    Blk d = sub(Dt, mul(Ut, Sf[type(l)], R), R);
+    if (cyclic || l > 0) d = sub(d, mul(Lt, Rl[type(wrap(l - 1))], R), R);
+    return d;
+  }
+};
+
+// Row l of the inverse over lanes l-K..l+K (a line of more than 2K+1 lanes, or
+// an acyclic one, whose absent lanes give zeros), by eliminating towards lane l
+// from both ends of the window.
+bool inverse_row(const Reduced &rs, int l, int K, std::vector<Blk> &g) {
+  const int R = rs.R;
+  g.assign(2 * K + 1, Blk());
+  auto there = [&](int j) { return rs.cyclic || (j >= 0 && j < rs.L); };
+  auto id = [&](int j) { return rs.cyclic ? rs.wrap(j) : j; };
+  std::vector<Blk> wl(K + 1), wr(K + 1);  // inverses of the eliminated diagonal blocks at distance 1..K
+  Blk centre = rs.diag(id(l));
+  for (int side = -1; side <= 1; side += 2) {
+    std::vector<Blk> &w = side < 0 ? wl : wr;
+    Blk corr;
+    bool have = false;
+    for (int d = K; d >= 1; --d) {
+      const int j = l + side * d;
+      if (!there(j)) continue;
+      Blk a = rs.diag(id(j));
+      if (have) a = sub(a, corr, R);
+      if (!invert(a, R, w[d])) return false;
+      // what lane j's elimination takes from the diagonal of its neighbour towards l
+      const int t = j - side;
+      const Blk to = side < 0 ? rs.lower(id(t)) : rs.upper(id(t));
+      const Blk from = side < 0 ? rs.upper(id(j)) : rs.lower(id(j));
+      corr = mul(mul(to, w[d], R), from, R);
+      have = true;
+    }
+    if (have) centre = sub(centre, corr, R);
+  }
+  if (!invert(centre, R, g[K])) return false;
+  for (int side = -1; side <= 1; side += 2)
+    for (int d = 1; d <= K; ++d) {
+      const int j = l + side * d, t = j - side;
+      if (!there(j)) break;
+      const Blk c = side < 0 ? rs.lower(id(t)) : rs.upper(id(t));
+      g[K + side * d] = neg(mul(mul(g[K + side * (d - 1)], c, R), (side < 0 ? wl : wr)[d], R), R);
+    }
+  return true;
+}
+
+}  // namespace window
+
+bool build_window(int n, int R, const double *bands, bool cyclic, int M, double tol, bool ring, WinLayout &w) {
+  using namespace window;
+  const int W = 2 * R + 1, N = M - R;
+  const int L = (n + M - 1) / M;
+  if (L < 2 || N < R + 1) return false;
+  ring = ring && n % M != 0;
+  if (ring ? !cyclic : ((n + L - 1) / L != M || n / L < 2 * R + 1)) return false;
+  w = WinLayout();
+  const int base = ring ? M : n / L, extra = ring ? 0 : n % L;
+  const bool two = extra > 0;  // lanes of two sizes
+  auto a = [&](int o) { return o < -R || o > R ? 0.0 : bands[o + R]; };
+  double scale = 0.0;
+  for (int o = 0; o < W; ++o) scale = std::max(scale, std::fabs(bands[o]));
+  // Toeplitz elimination of N + R rows (the rows beyond N only complete u)
+  const int NE = N + R;
+  std::vector<double> k((size_t)NE * R, 0.0), u((size_t)NE * R, 0.0), dinv(NE);
+  {
+    std::vector<double> c((size_t)NE * W, 0.0);
+    for (int j = 0; j < NE; ++j)
+      for (int o = -R; o <= R; ++o)
+        if (j + o >= 0 && j + o < NE) c[(size_t)j * W + o + R] = a(o);
+    for (int j = 0; j < NE; ++j) {
+      const double piv = c[(size_t)j * W + R];
+      if (!(std::fabs(piv) > 1e-2 * scale) || !std::isfinite(piv)) return false;
+      dinv[j] = 1.0 / piv;
+      for (int i = j + 1; i <= std::min(NE - 1, j + R); ++i) {
+        const double f = c[(size_t)i * W + (j - i + R)] / piv;
+        k[(size_t)i * R + (i - j) - 1] = f;
+        for (int q = j + 1; q <= std::min(NE - 1, j + R); ++q) c[(size_t)i * W + (q - i + R)] -= f * c[(size_t)j * W + (q - j + R)];
+      }
+      for (int q = 1; q <= R; ++q) u[(size_t)j * R + q - 1] = j + q < NE ? c[(size_t)j * W + R + q] * dinv[j] : 0.0;
+    }
+  }
+  auto forward = [&](int m, double *x) {
+    for (int j = 1; j < m; ++j)
+      for (int q = 1; q <= R && q <= j; ++q) x[j] -= k[(size_t)j * R + q - 1] * x[j - q];
+  };
+  auto backward = [&](int m, double *x) {
+    for (int j = m - 1; j >= 0; --j) {
+      double s = x[j] * dinv[j];
+      for (int q = 1; q <= R && j + q < m; ++q) s -= u[(size_t)j * R + q - 1] * x[j + q];
+      x[j] = s;
+    }
+  };
+  Reduced rs;
+  rs.R = R;
+  rs.L = L;
+  rs.extra = extra;
+  rs.cyclic = cyclic;
+  for (int i = 0; i < R; ++i)
+    for (int c = 0; c < R; ++c) {
+      rs.Lt.v[i * R + c] = a(c - R - i);
+      rs.Dt.v[i * R + c] = a(c - i);
+      rs.Ut.v[i * R + c] = a(R + c - i);
+    }
+  // the row table
+  const int RW = win_row_size(R);
+  w.coef.assign((size_t)N * RW + 2 * R * R, 0.0);
+  std::vector<double> wf((size_t)R * N, 0.0);  // first R rows of U^{-1}
+  for (int i = 0; i < R; ++i) {
+    std::vector<double> p(N + R, 0.0);
+    p[i] = 1.0;
+    for (int j = i; j < N; ++j) {
+      wf[(size_t)i * N + j] = p[j] * dinv[j];
+      for (int q = 1; q <= R; ++q) p[j + q] -= p[j] * u[(size_t)j * R + q - 1];
+    }
+  }
+  double biggest = 0.0;
+  std::vector<double> col(N);
+  for (int c = 0; c < R; ++c) {
+    for (int j = 0; j < N; ++j) col[j] = a(c - R - j);
+    forward(N, col.data());
+    for (int j = 0; j < N; ++j) w.coef[(size_t)j * RW + 2 * R + c] = col[j];
+  }
+  for (int j = 0; j < N; ++j) {
+    double *row = w.coef.data() + (size_t)j * RW;
+    for (int q = 0; q < R; ++q) {
+      row[q] = k[(size_t)j * R + q];
+      row[3 * R + 1 + q] = u[(size_t)j * R + q];
+      for (int i = 0; i < R; ++i) row[R + q] += rs.Ut.v[q * R + i] * wf[(size_t)i * N + j];
+    }
+    row[3 * R] = dinv[j];
+    for (int q = 0; q < RW; ++q)
+      if (q != 3 * R) biggest = std::max(biggest, std::fabs(row[q]));
+  }
+  if (!(biggest <= 64.0 * std::max(1.0, scale))) return false;  // elimination that grows needs pivoting
+  for (int ty = 0; ty < 2; ++ty) {
+    const int m = ty == 0 || !two ? N : N - 1;  // interior rows of this lane size
+    // z: L~ times the last R rows of U^{-1}, on the last R values of z
+    double *z = w.coef.data() + (size_t)N * RW + ty * R * R;
+    for (int i = 0; i < R; ++i) {
+      std::vector<double> e(m, 0.0);
+      e[m - R + i] = 1.0;
+      backward(m, e.data());
+      for (int s = 0; s < R; ++s)
+        for (int b = 0; b < R; ++b) z[b * R + i] += rs.Lt.v[b * R + s] * e[m - R + s];
+    }
+    for (int c = 0; c < R; ++c) {
+      std::vector<double> x(m);
+      for (int j = 0; j < m; ++j) x[j] = a(c - R - j);
+      forward(m, x.data());
+      backward(m, x.data());
+      for (int s = 0; s < R; ++s) {
+        rs.Sf[ty].v[s * R + c] = x[s];
+        rs.Sl[ty].v[s * R + c] = x[m - R + s];
+      }
+      for (int j = 0; j < m; ++j) x[j] = a(m + c - j);
+      forward(m, x.data());
+      backward(m, x.data());
+      for (int s = 0; s < R; ++s) {
+        rs.Rf[ty].v[s * R + c] = x[s];
+        rs.Rl[ty].v[s * R + c] = x[m - R + s];
+      }
+    }
+  }
+  // window half-width from a line of the smaller lanes (the slowest decay)
+  constexpr int K0 = 2 * kWinMaxD;
+  std::vector<Blk> g;
+  int D = 0;
+  {
+    Reduced all = rs;
+    all.L = 4 * K0;
+    all.extra = 0;
+    all.cyclic = true;
+    double sum = 0.0, out = 0.0;
+    bool ok = inverse_row(all, 0, K0, g);
+    if (ok) {
+      for (const Blk &b : g) sum += abs_sum(b, R);
+      D = K0;
+      while (D > 0 && out + abs_sum(g[K0 - D], R) + abs_sum(g[K0 + D], R) <= tol * sum) {
+        out += abs_sum(g[K0 - D], R) + abs_sum(g[K0 + D], R);
+        --D;
+      }
+      ok = std::isfinite(sum) && sum * scale <= 1e4;
+    }
+    if (!ok) D = K0;
+  }
+  D = std::max(D, 1);
+  // a short line's window holds every lane (nothing is left out)
+  const bool whole = cyclic && !ring && D >= L / 2;
+  if (whole) D = std::max(1, L / 2);
+  if (D > kWinMaxD) return false;
+  w.M = M;
+  w.L = L;
+  w.base = base;
+  w.extra = extra;
+  w.D = D;
+  w.uniform = cyclic && !two ? 1 : 0;
+  const int K = D + 3, RR = R * R;
+  w.gidx.assign(L, 0);
+  auto put = [&](const std::vector<Blk> &row, int centre) {
+    for (int d = -D; d <= D; ++d)
+      for (int q = 0; q < RR; ++q) w.g.push_back(row[centre + d].v[q]);
+  };
+  if (ring) {  // lanes around the line without end
+    put(g, K0);
+    return true;
+  }
+  if (cyclic && L < 2 * K + 2) {  // few lanes: the dense inverse
+    const int m = L * R;
+    std::vector<double> t((size_t)m * m, 0.0), inv((size_t)m * m);
+    for (int l = 0; l < L; ++l) {
+      const int lm = rs.wrap(l - 1), lp = rs.wrap(l + 1);
+      const Blk lo = rs.lower(l), di = rs.diag(l), up = rs.upper(l);
+      for (int i = 0; i < R; ++i)
+        for (int c = 0; c < R; ++c) {
+          t[(size_t)(l * R + i) * m + lm * R + c] += lo.v[i * R + c];
+          t[(size_t)(l * R + i) * m + l * R + c] += di.v[i * R + c];
+          t[(size_t)(l * R + i) * m + lp * R + c] += up.v[i * R + c];
+        }
+    }
+    if (!invert(m, t.data(), inv.data())) return w.M = 0, false;
+    const int rows = w.uniform ? 1 : L;
+    for (int l = 0; l < rows; ++l) {
+      std::vector<Blk> row(2 * D + 1);
+      for (int d = -D; d <= D; ++d) {
+        if (2 * D >= L && d == -D && L % 2 == 0) continue;  // lane l - L/2 is lane l + L/2
+        if (d < -((L - 1) / 2) || d > L / 2) continue;
+        const int j = rs.wrap(l + d);
+        for (int i = 0; i < R; ++i)
+          for (int c = 0; c < R; ++c) row[D + d].v[i * R + c] = inv[(size_t)(l * R + i) * m + j * R + c];
+      }
+      put(row, D);
+      w.gidx[l] = l;
+    }
+    return true;
+  }
+  // Lanes share a row when the sizes of the lanes in their window lie alike
+  // (the inverse of the reduced system is the inverse of A at the interface
+  // rows, in a cyclic line a function of the distance between them alone); in
+  // an acyclic line also those beyond it, up to where its ends are felt
+  std::map<std::vector<int>, int> seen;
+  for (int l = 0; l < L; ++l) {
+    if (w.uniform && l > 0) break;
+    std::vector<int> key;
+    const int reach = cyclic ? D : K + 1;
+    for (int d = -reach; d < reach; ++d) {
+      const int j = l + d;
+      key.push_back(!cyclic && (j < 0 || j >= L) ? 2 : rs.type(rs.wrap(j)));
+    }
+    auto it = seen.find(key);
+    if (it != seen.end()) {
+      w.gidx[l] = it->second;
+      continue;
+    }
+    if (!inverse_row(rs, l, K, g)) return w.M = 0, false;
+    const int at = (int)seen.size();
+    seen[key] = at;
+    w.gidx[l] = at;
+    put(g, K);
+  }
+  return true;
+}
+
+}  // namespace cb
