@@ -421,6 +421,7 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
   auto split = [&](int most) {
     const int own = parts ? (wl.L + parts - 1) / parts : most - 2 * halo;
     if (own + 2 * halo > most || (own < 8 && own < wl.L)) return false;
+    a.ring = 1;
     a.H = halo;
     a.nch = (wl.L + own - 1) / own;
     a.Lc = (wl.L + a.nch - 1) / a.nch;
@@ -950,6 +951,7 @@ cb_status cb_rhs_stencil(const cb_stencil *stencil, const cb_grid *grid, int32_t
   if (!f || !b) return fail(CB_ERR_INVALID_ARG, "f and b must be non-NULL");
   if (overlap(f, b, span_elems(grid))) return fail(CB_ERR_INVALID_ARG, "f and b overlap");
   StencilArgs a;
+  std::memset(&a, 0, sizeof(a));
   a.f = f;
   a.b = b;
   a.n = g.n;
@@ -961,10 +963,71 @@ cb_status cb_rhs_stencil(const cb_stencil *stencil, const cb_grid *grid, int32_t
   a.lo = stencil->lo;
   a.hi = stencil->hi;
   for (int i = 0; i < 7; ++i) a.c[i] = i <= stencil->hi - stencil->lo ? stencil->coef[i] : 0.0;
-  const int64_t blocks = (a.total + 255) / 256;
+  int64_t blocks = (a.total + 255) / 256;
   if (blocks > 0x7fffffff) return fail(CB_ERR_UNSUPPORTED, "grid too large for one launch");
+  // unit-stride lines: windowed lanes of 16 rows, of which only the stencil runs
+  constexpr int M = 16;
+  if (a.rs == 1 && g.n >= 2 * M && g.n < (1 << 30) && g.nlines < (int64_t(1) << 31)) {
+    const int Q = stencil->lo >= -2 && stencil->hi <= 2 ? 2 : 3, QP = (Q + 1) & ~1;
+    WinLaunch w;
+    std::memset(&w.a, 0, sizeof(w.a));
+    WinArgs &s = w.a;
+    w.k = find_win_stencil_kernel(Q);
+    s.in = f;
+    s.out = b;
+    s.nlines = g.nlines;
+    s.su = g.su;
+    s.sv = g.sv;
+    s.rs = 1;
+    s.nudiv = make_divmagic((uint32_t)g.nu);
+    s.n = (int)g.n;
+    s.base = M;
+    s.L = (s.n + M - 1) / M;
+    s.ring = s.L > 64 || s.L * M != s.n;
+    s.nch = (s.L + 63) / 64;
+    s.Lc = (s.L + s.nch - 1) / s.nch;
+    s.Lw = s.Lc;
+    s.lpw = 64 / s.Lw;
+    s.linv = (65536 + s.Lw - 1) / s.Lw;
+    s.W = 4 * s.lpw;
+    s.pitch = (s.Lw * (M + 1) + 2 * QP + 4) & ~1;
+    s.chunk_fast = 1;
+    s.xcds = 1;
+    s.one = -1;
+    s.nt = 1;
+    s.lo = stencil->lo;
+    s.hi = stencil->hi;
+    stencil_q(stencil, s.stc);
+    w.threads = 256;
+    w.lds = ((size_t)w.k->lds * s.W * (s.Lw + 2) + (size_t)s.W * s.pitch) * sizeof(double);
+    const int64_t ltiles = (g.nlines + s.W - 1) / s.W;
+    w.blocks = ltiles * s.nch;
+    s.ltiles = (uint32_t)ltiles;
+    if (w.blocks <= 0x7fffffff && w.lds <= lds_cap()) return launch_win(w, static_cast<hipStream_t>(stream));
+  }
+  // strided lines next to each other: pairs of them, 32-bit tile indices
+  int form = STENCIL_ANY;
+  if (a.rs != 1 && g.su == 1 && g.n < (1 << 30)) {
+    int64_t nv = g.nlines / g.nu;
+    if (g.sv == g.nu && g.nlines < (int64_t(1) << 31)) {  // one run across planes
+      a.nu = g.nlines;
+      nv = 1;
+    }
+    a.nt = a.rs % 16 == 0 && (nv == 1 || a.sv % 16 == 0) && (uintptr_t)b % 128 == 0;  // whole cache lines
+    const int per = 4 * (a.nt ? kStencilRows / 2 : kStencilRows);
+    const int64_t runs = (a.nu + 127) / 128, rows = (g.n + per - 1) / per;
+    if (a.nu < (int64_t(1) << 31) && runs * rows * nv < (int64_t(1) << 31)) {
+      form = a.nt ? STENCIL_S_SHORT : STENCIL_S;
+      a.dq = make_divmagic((uint32_t)runs);
+      a.du = make_divmagic((uint32_t)rows);
+      blocks = runs * rows * nv;
+      a.xcds = xcd_count();
+    } else {
+      a.nu = g.nu;
+    }
+  }
   void *args[] = {&a};
-  hipError_t e = hipLaunchKernel(stencil_kernel(), dim3((unsigned)blocks), dim3(256), args, 0,
+  hipError_t e = hipLaunchKernel(stencil_kernel(form), dim3((unsigned)blocks), dim3(256), args, 0,
                                  static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   return CB_OK;

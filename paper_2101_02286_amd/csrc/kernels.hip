@@ -10,12 +10,84 @@
 #include "launch.h"
 #include "line.h"
 #include "wg.h"
+#include "win.h"
 
 namespace cb {
 
 // ------------------------------------------------------------------------
-// Standalone periodic stencil b = sum_q c_q f_{j+q} along one axis.
+// Standalone periodic stencil b = sum_q c_q f_{j+q} along one axis: bound by
+// HBM (16 B per point).  Each value is read from memory once and from the
+// caches, LDS or registers for its other taps; the taps add up in order of q.
+// Unit-stride lines go through the LDS tile of the windowed lanes (win.h):
+// direct 16-byte loads of every tap ran at 2.4-3.7 TB/s, bound by the address
+// unit, against 5.3-5.9.  Sixth-order weights, one 256 x 200 x 384 pass along x
+// and y each: one point per thread and 64-bit divisions 136 us, now 54 and 64.
 // ------------------------------------------------------------------------
+typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));  // any 8-byte address
+
+static const WinKernel kWinStencil[] = {CB_WIN_STENCIL(2), CB_WIN_STENCIL(3)};
+const WinKernel *find_win_stencil_kernel(int Q) { return &kWinStencil[Q > 2 ? 1 : 0]; }
+
+__device__ __forceinline__ int wrap_row(int j, int n) {
+  while (j < 0) j += n;
+  while (j >= n) j -= n;
+  return j;
+}
+
+// Strided lines that lie next to each other: a wavefront takes 64 pairs of
+// adjacent lines and kRows rows of them, of which it keeps the last seven in
+// registers (row addresses are the same for all its threads).  8 rows measured
+// 2-7 % faster than 16 on rows that are whole cache lines, up to 10 % slower on
+// others, which gain more from rows that stay close in time.
+template <int kRows>
+__global__ __launch_bounds__(256) void k_stencil_s(const StencilArgs a) {
+  const FastDiv fq{a.dq.d, a.dq.mul, a.dq.s1, a.dq.s2}, fu{a.du.d, a.du.mul, a.du.s1, a.du.s2};
+  uint32_t tile = blockIdx.x;
+  if (a.xcds > 1) {  // neighbouring tiles share rows: on one XCD, as in k_line
+    const uint32_t X = (uint32_t)a.xcds, G = gridDim.x, q = G / X, rem = G % X, x = tile % X, s = tile / X;
+    tile = x * q + (x < rem ? x : rem) + s;
+  }
+  // tile -> (run of 64 pairs of lines, 4 runs of rows)
+  const uint32_t rest = fq.div(tile), pt = tile - rest * a.dq.d;
+  const uint32_t v = fu.div(rest), jt = rest - v * a.du.d;
+  const int n = (int)a.n;
+  const int j0 = __builtin_amdgcn_readfirstlane(((int)jt * 4 + (int)(threadIdx.x >> 6)) * kRows);
+  const uint32_t u = 2 * (pt * 64 + (threadIdx.x & 63));
+  if (j0 >= n || u >= (uint32_t)a.nu) return;
+  const bool one = u + 1 == (uint32_t)a.nu;
+  const int64_t base = (int64_t)u + (int64_t)v * a.sv;
+  const double *f = a.f + base;
+  double *b = a.b + base;
+  auto load = [&](int j) -> dbl2u {
+    const double *p = f + (int64_t)wrap_row(j, n) * a.rs;
+    if (one) return dbl2u{*p, 0.0};
+    return *reinterpret_cast<const dbl2u *>(p);
+  };
+  dbl2u w[7];
+#pragma unroll
+  for (int q = -3; q < 3; ++q) w[q + 3] = q >= a.lo && q < a.hi ? load(j0 + q) : dbl2u{0.0, 0.0};
+#pragma unroll
+  for (int k = 0; k < kRows; ++k) {
+    if (j0 + k >= n) break;
+    // the row that enters: the highest tap's
+    const dbl2u next = load(j0 + k + a.hi);
+#pragma unroll
+    for (int q = -3; q <= 3; ++q)
+      if (q == a.hi) w[q + 3] = next;
+    dbl2u acc = {0.0, 0.0};
+#pragma unroll
+    for (int q = -3; q <= 3; ++q)
+      if (q >= a.lo && q <= a.hi) acc += a.c[q - a.lo] * w[q + 3];
+    double *p = b + (int64_t)(j0 + k) * a.rs;
+    if (one) *p = acc.x;
+    else if (a.nt) __builtin_nontemporal_store(acc, reinterpret_cast<dbl2u *>(p));
+    else *reinterpret_cast<dbl2u *>(p) = acc;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) w[q] = w[q + 1];
+  }
+}
+
+// Any positive strides and any size.
 __global__ __launch_bounds__(256) void k_stencil(const StencilArgs a) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= a.total) return;
@@ -37,7 +109,8 @@ __global__ __launch_bounds__(256) void k_stencil(const StencilArgs a) {
   double acc = 0.0;
   for (int q = a.lo; q <= a.hi; ++q) {
     int64_t jj = j + q;
-    jj = jj < 0 ? jj + a.n : (jj >= a.n ? jj - a.n : jj);
+    while (jj < 0) jj += a.n;
+    while (jj >= a.n) jj -= a.n;
     acc += a.c[q - a.lo] * a.f[base + jj * a.rs];
   }
   a.b[base + j * a.rs] = acc;
@@ -119,7 +192,11 @@ const WinKernel *find_win_kernel(int R, int M, int prec, int mode, int Q, bool u
   return nullptr;
 }
 
-const void *stencil_kernel() { return (const void *)&k_stencil; }
+const void *stencil_kernel(int form) {
+  return form == STENCIL_S         ? (const void *)&k_stencil_s<kStencilRows>
+         : form == STENCIL_S_SHORT ? (const void *)&k_stencil_s<kStencilRows / 2>
+                                   : (const void *)&k_stencil;
+}
 
 const BatchKernel *find_batch_kernel(int R, int M, int fp32, bool uni, bool ilu, int mode, int Q) {
   int cnt = 0;

@@ -53,6 +53,7 @@ struct WinArgs {
   DivMagic nudiv;            // line -> (u, v)
   int n, L, base, extra;     // the line's lanes (WinLayout)
   int Lw, H, Lc, nch;        // lanes of a line in one workgroup, halo lanes per side, lanes stored, chunks per line
+  int ring;                  // the workgroup's lanes are a window of the line, not all of it
   int D, acyclic, W;         // window half-width; lines (strided rows: pairs of lines) per tile
   int lgW, one;              // strided rows: log2 W; the pair of a row of lines that holds one line, or -1
   int lpw;                   // unit-stride rows: lines per wavefront
@@ -64,6 +65,7 @@ struct WinArgs {
   int nt, gcount;            // streaming loads and stores; values in g
   const void *coef, *g;
   const int *gidx;
+  int lo, hi;                // stencil by itself: its taps
   double stc[7];             // stencil coefficients for q = -3..3
   double bands[2 * kMaxR + 1];
 };
@@ -109,9 +111,14 @@ struct StencilArgs {
   const double *f;
   double *b;
   int64_t total, n, nu, su, sv, rs;
-  int lo, hi;
+  DivMagic dq, du;  // STENCIL_S: runs of lines, runs of rows per plane
+  int lo, hi, nt, xcds;
   double c[7];
 };
+// Forms of the stencil kernel: strided lines next to each other (workgroups of
+// 4 x kStencilRows rows, or half as many), anything.
+enum { STENCIL_ANY = 0, STENCIL_S = 1, STENCIL_S_SHORT = 2 };
+constexpr int kStencilRows = 16;
 
 struct LineKernel {
   int R, M, fp32, mode, Q;
@@ -193,6 +200,7 @@ const WgKernel *find_wg_kernel(int R, int M, int mode, int Q, bool ilu);
 const WgKernel *find_wg32_kernel(int R, int M, int mode, int Q, bool ilu);
 const WinKernel *find_win_kernel(int R, int M, int prec, int mode, int Q, bool uni);
 const WinKernel *find_win_copy_kernel(int M, int mode, bool uni);
-const void *stencil_kernel();
+const void *stencil_kernel(int form);
+const WinKernel *find_win_stencil_kernel(int Q);  // unit-stride lines, 16-row lanes
 
 }  // namespace cb

@@ -279,9 +279,13 @@ __device__ __forceinline__ void win_store2(dbl2 v, double *q) {
 }
 template <bool B> struct WinFlag { static constexpr bool value = B; };
 
+// What a tile's rows go through between their loads and their stores: the
+// stencil (Q > 0) and the solve, nothing, or the stencil alone.
+enum { WIN_SOLVE = 0, WIN_MOVE = 1, WIN_STENCIL = 2 };
+
 // One tile: the lanes of W lines (pairs of lines), or of one run of lanes
 // (chunk) of each of them with H halo lanes on either side.
-template <int R, int M, typename T, bool REF, int MODE, int Q, bool UNI, bool COPY>
+template <int R, int M, typename T, bool REF, int MODE, int Q, bool UNI, int OP>
 __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double *smem) {
   constexpr int QQ = Q > 0 ? Q : 1;
   constexpr int KT = Q > 0 ? M + 2 : M;  // tile rows a lane loads (a window's halo needs one or two more)
@@ -292,7 +296,7 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
   p.Lw = a.Lw;
   p.D = a.D;
   p.block = MODE == MODE_S;
-  p.whole = a.H == 0;
+  p.whole = !a.ring;
   int li;
   if (MODE == MODE_S) {
     p.l = tid >> a.lgW;
@@ -362,11 +366,11 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
   if constexpr (MODE == MODE_X) {
     tb = smem + (size_t)win_planes(R, Q, REF, MODE) * p.NS + (size_t)li * a.pitch + QP + 2;
     len = a.n;
-    if (H > 0) {
+    if (a.ring) {
       r0 = ((int)ch * a.Lc - H) * M;
       len = (own + 2 * H) * M;
     }
-    const int e0 = H > 0 ? -QP : 0, e1 = H > 0 ? len + QP : len;
+    const int e0 = a.ring ? -QP : 0, e1 = a.ring ? len + QP : len;
     // pairs of rows from any 8-byte address (r0, len and QP are even); the ring
     // wraps between the rows of a pair when n is odd
     auto load = [&](auto nt) {
@@ -412,16 +416,16 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
       for (int k = 0; k < M; ++k)
         b64[k] = (active && (UNI || k < M - 1 || !sh)) ? win_load2<false>(in + k * a.rs, true) : zero;
     }
-    if (Q > 0 && !COPY) {
+    if (Q > 0 && OP == WIN_SOLVE) {
       // the window's ends take their halo from memory
 #pragma unroll
       for (int i = 0; i < QQ; ++i) {
         gp[i] = gn[i] = zero;
-        if (H > 0 && active && p.l == 0) {
+        if (a.ring && active && p.l == 0) {
           const int r = start - Q + i;
           gp[i] = win_load2<false>(lin + (int64_t)(r < 0 ? r + a.n : r) * a.rs, one);
         }
-        if (H > 0 && active && p.l == own + 2 * H - 1) {
+        if (a.ring && active && p.l == own + 2 * H - 1) {
           const int r = start + m + i;
           gn[i] = win_load2<false>(lin + (int64_t)(r >= a.n ? r - a.n : r) * a.rs, one);
         }
@@ -431,25 +435,25 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
   // lanes of two sizes read different rows of the window table: copied to LDS
   // (visible after the next exchange)
   T *gl = reinterpret_cast<T *>(smem + (size_t)win_planes(R, Q, REF, MODE) * win_lines(MODE) * p.NS);
-  if (!UNI && !COPY) {
+  if (!UNI && OP == WIN_SOLVE) {
     const T *gw = static_cast<const T *>(a.g);
     for (int i = tid; i < a.gcount; i += blockDim.x) gl[i] = gw[i];
   }
-  if (Q > 0 && !COPY) {  // fused right-hand-side stencil (Eqs. (1)-(2)), periodic
+  if (Q > 0 && OP != WIN_MOVE) {  // fused right-hand-side stencil (Eqs. (1)-(2)), periodic
     VD fp[QQ], fn[QQ], tail[QQ + 1];
     if constexpr (MODE == MODE_X) {
 #pragma unroll
       for (int i = 0; i < QQ; ++i) {
         // the last rows of the lane before and the first of the next one
         int e = p.l * (M + 1) - 1 - Q + i, f = (p.l + 1) * (M + 1) + i;
-        if (p.l == 0 && H == 0) e = a.Lw * (M + 1) - 1 - Q + i;
-        if (p.l == a.Lw - 1 && H == 0) f = i;
+        if (p.l == 0 && !a.ring) e = a.Lw * (M + 1) - 1 - Q + i;
+        if (p.l == a.Lw - 1 && !a.ring) f = i;
         fp[i] = active ? tb[e] : 0.0;
         fn[i] = active ? tb[f] : 0.0;
       }
     } else {
       win_halo<QQ, M, UNI, VD>(b64, sh, p, reinterpret_cast<VD *>(smem), fp, fn);
-      if (H > 0) {
+      if (a.ring) {
 #pragma unroll
         for (int i = 0; i < QQ; ++i) {
           fp[i] = p.l == 0 ? gp[i] : fp[i];
@@ -463,13 +467,14 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
     for (int k = 0; k < M; ++k) {
       VD acc = zero;
 #pragma unroll
-      for (int q = -Q; q <= Q; ++q) acc += a.stc[q + 3] * win_at<QQ, M, VD>(b64, fp, tail, k + q);
+      for (int q = -Q; q <= Q; ++q)  // (the stencil by itself: its own taps only, as 0 x inf is not 0)
+        if (OP == WIN_SOLVE || (q >= a.lo && q <= a.hi)) acc += a.stc[q + 3] * win_at<QQ, M, VD>(b64, fp, tail, k + q);
       bb[k] = (!UNI && k == M - 1 && sh) ? zero : acc;
     }
 #pragma unroll
     for (int k = 0; k < M; ++k) b64[k] = bb[k];
   }
-  if (!COPY) {
+  if (OP == WIN_SOLVE) {
     const T *cf = static_cast<const T *>(a.coef);
     const T *gw = static_cast<const T *>(a.g);
     const int gi = UNI ? 0 : a.gidx[g], gin = UNI ? 0 : a.gidx[g + 1 < a.L ? g + 1 : 0];
@@ -530,14 +535,14 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
     }
   }
   if constexpr (MODE == MODE_X) {
-    if (COPY) p.sync();
+    if (OP != WIN_SOLVE) p.sync();  // (the solve's exchange lies in between)
 #pragma unroll
     for (int k = 0; k < M; ++k)
       if (active) tb[p.l * (M + 1) + k] = b64[k];
     p.sync();
     double *lout = a.out + lbase;
     int s0 = 0, s1 = len;  // tile words this tile stores
-    if (H > 0) {
+    if (a.ring) {
       s0 = H * M;
       const int rows = a.n - (int)ch * a.Lc * M;
       s1 = s0 + (rows < own * M ? rows : own * M);
@@ -582,7 +587,7 @@ constexpr int win_max_threads() {
   return MODE == MODE_X ? 256 : 1024;
 }
 
-template <int R, int M, typename T, bool REF, int MODE, int Q, bool UNI, bool COPY = false>
+template <int R, int M, typename T, bool REF, int MODE, int Q, bool UNI, int OP = WIN_SOLVE>
 __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win(const WinArgs a) {
   extern __shared__ __align__(16) double smem[];
   uint32_t tile = blockIdx.x;
@@ -591,7 +596,7 @@ __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win(const WinA
     const uint32_t j = tile % X, s = tile / X;
     tile = j * q + (j < rem ? j : rem) + s;
   }
-  win_tile<R, M, T, REF, MODE, Q, UNI, COPY>(a, tile, smem);
+  win_tile<R, M, T, REF, MODE, Q, UNI, OP>(a, tile, smem);
 }
 
 // Batched launch over the tiles of many items of one instance, as k_batched.
@@ -624,7 +629,7 @@ __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win_batched(Ba
       const uint32_t X = (uint32_t)it.a.xcds, q = G / X, rem = G % X, j = local % X, s = local / X;
       local = j * q + (j < rem ? j : rem) + s;
     }
-    win_tile<R, M, T, REF, MODE, Q, UNI, false>(it.a, local, smem);
+    win_tile<R, M, T, REF, MODE, Q, UNI, WIN_SOLVE>(it.a, local, smem);
     return;
   }
   for (;;) {
@@ -635,7 +640,7 @@ __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win_batched(Ba
     __syncthreads();
     if (t >= total) break;
     const WinItemDev &it = items[item_of(t)];
-    win_tile<R, M, T, REF, MODE, Q, UNI, false>(it.a, (uint32_t)(t - it.tile_begin), smem);
+    win_tile<R, M, T, REF, MODE, Q, UNI, WIN_SOLVE>(it.a, (uint32_t)(t - it.tile_begin), smem);
     __syncthreads();
   }
   if (threadIdx.x == 0) {
@@ -662,6 +667,12 @@ const void *win_batched() {
 #define CB_WIN_U(R, M, T, REF, MODE, U) \
   CB_WIN_INST(R, M, T, REF, MODE, 0, U), CB_WIN_INST(R, M, T, REF, MODE, 2, U), CB_WIN_INST(R, M, T, REF, MODE, 3, U)
 #define CB_WIN_X(R, M, T, REF) CB_WIN_U(R, M, T, REF, MODE_X, true)
+// the stencil by itself on unit-stride lines, in lanes of 16 rows
+#define CB_WIN_STENCIL(Q)                                                                              \
+  WinKernel {                                                                                          \
+    1, 16, 0, MODE_X, Q, true, win_max_threads<MODE_X>(), win_planes(1, Q, false, MODE_X),             \
+        (const void *)&k_win<1, 16, double, false, MODE_X, Q, true, WIN_STENCIL>, nullptr              \
+  }
 #define CB_WIN_S(R, M, T, REF) CB_WIN_U(R, M, T, REF, MODE_S, false), CB_WIN_U(R, M, T, REF, MODE_S, true)
 
 }  // namespace cb

@@ -39,6 +39,12 @@ WINDOWED = """
 1 1700 1 33 1 0 0 0 0 0 0 0
 1 2048 0 2 2 0 1 0 0 0 4 0
 2 2048 1 17 2 0 1 0 0 0 8 1
+0 32 0 5 3 0 1 2 0 0 0 0
+0 33 0 7 2 1 1 3 0 0 0 0
+0 48 0 3 3 0 1 2 0 0 0 0
+0 1024 0 3 2 0 1 3 0 0 0 0
+0 1025 0 3 2 1 1 1 0 0 0 0
+0 2071 0 2 2 0 1 3 0 0 0 0
 """
 # in place in several chunks, and unit-stride acyclic lines: the general kernels
 GENERAL = """

@@ -3,7 +3,7 @@
 // C ABI, against the oracle.  Reads one case per line:
 //   r n axis d0 d1 pitch cyclic halfwidth precision in_place partitions batch
 // (d0, d1: the other extents in axis order; pitch: spare elements per x row;
-// halfwidth 0: plain solve) and prints "ok" or "BAD", whether a windowed kernel
+// halfwidth 0: plain solve; r = 0: the stencil by itself) and prints "ok" or "BAD", whether a windowed kernel
 // ran, and the relative error.
 #include <hip/hip_runtime.h>
 #include <pthread.h>
@@ -49,7 +49,11 @@ const WgKernel *find_wg_kernel(int, int, int, int, bool) {
   return &k;
 }
 const WgKernel *find_wg32_kernel(int, int, int, int, bool) { return nullptr; }
-const void *stencil_kernel() { return nullptr; }
+const void *stencil_kernel(int) { return nullptr; }
+const WinKernel *find_win_stencil_kernel(int Q) {
+  static const WinKernel k[2] = {CB_WIN_STENCIL(2), CB_WIN_STENCIL(3)};
+  return &k[Q > 2 ? 1 : 0];
+}
 }  // namespace cb
 
 static pthread_barrier_t g_block;
@@ -103,8 +107,8 @@ int main() {
     d.cyclic = cyclic;
     d.precision = prec;
     d.partitions = parts;
-    cb_plan_t p;
-    if (cb_plan(&d, &p) != CB_OK) return printf("plan: %s\n", cb_last_error()), 1;
+    cb_plan_t p = nullptr;
+    if (r && cb_plan(&d, &p) != CB_OK) return printf("plan: %s\n", cb_last_error()), 1;
     cb_grid g;
     const int other[2] = {d0, d1};
     for (int i = 0, k = 0; i < 3; ++i) g.n[i] = i == axis ? n : other[k++];
@@ -124,7 +128,9 @@ int main() {
     for (int q = 0; q <= 2 * half && half; ++q) st.coef[q] = 0.3 * (q - half) + 0.1 * (q == half);
     g_windowed = 0;
     cb_status s;
-    if (batch) {
+    if (!r) {
+      s = cb_rhs_stencil(&st, &g, axis, in, out, nullptr);
+    } else if (batch) {
       cb_batch_item it = {p, half ? &st : nullptr, g, axis, in, out};
       std::vector<char> ws(cb_batch_workspace_bytes(&it, 1));
       s = cb_solve_batched(&it, 1, ws.data(), ws.size(), 1, nullptr);
@@ -144,7 +150,8 @@ int main() {
           for (int q = -half; q <= half && half; ++q)
             rhs[j] += st.coef[q + half] * b0[base + ((j + q + n) % n) * g.stride[axis]];
         }
-        orc_solve_lines(r, n, kBands[r].data(), 0, cyclic, 1, rhs.data(), x.data());
+        x = rhs;
+        if (r) orc_solve_lines(r, n, kBands[r].data(), 0, cyclic, 1, rhs.data(), x.data());
         for (int j = 0; j < n; ++j) {
           const int64_t at = base + j * g.stride[axis];
           inside[at] = 1;
@@ -158,7 +165,7 @@ int main() {
            ok ? "ok" : "BAD", ran, err / top, r, n, axis, d0, d1, pitch, cyclic, half, prec, in_place, parts, batch);
     fflush(stdout);
     bad += !ok;
-    cb_plan_destroy(p);
+    if (r) cb_plan_destroy(p);
     delete[] in;
     if (!in_place) delete[] out;
   }
