@@ -55,7 +55,9 @@ typedef enum {
 typedef enum {
   CB_FP64 = 0,        /* every step in FP64 */
   CB_FP32 = 1,        /* reduction arithmetic in FP32, FP64 input/output */
-  CB_FP32_REFINE = 2  /* FP32 reduction + FP64 residual iterative refinement */
+  CB_FP32_REFINE = 2  /* FP32 reduction + FP64 residual iterative refinement, or
+                         an FP64 solve where that takes less time (constant
+                         bands and automatic launch parameters) */
 } cb_precision;
 
 typedef struct cb_plan_s *cb_plan_t;

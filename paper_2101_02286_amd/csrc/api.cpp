@@ -152,8 +152,7 @@ cb_status upload(Plan &p) {
   for (int i = 0; i < 2; ++i) {
     const WinLayout &w = *wins[i];
     if (!w.M) continue;
-    const bool f64 = p.precision == CB_FP64;
-    wo[i] = {f64 ? ar.add(w.coef) : ar.add(to_f32(w.coef)), f64 ? ar.add(w.g) : ar.add(to_f32(w.g)), ar.add(w.gidx)};
+    wo[i] = {ar.add(w.coef), ar.add(w.g), ar.add(w.gidx)};
   }
   const size_t o_bands = ar.add(p.bands);
   size_t o_wg = 0, o_sr = 0, o_sroff = 0, o_ltut = 0, o_ro = 0, o_src = 0, o_mats = 0, o_bfun = 0;
@@ -208,8 +207,8 @@ cb_status upload(Plan &p) {
   p.dev_base = d;
   p.dev_bytes = (int64_t)ar.host.size();
   for (int i = 0; i < 2; ++i) {
-    wins[i]->d_coef = base + wo[i].c;
-    wins[i]->d_g = base + wo[i].g;
+    wins[i]->d_coef = reinterpret_cast<double *>(base + wo[i].c);
+    wins[i]->d_g = reinterpret_cast<double *>(base + wo[i].g);
     wins[i]->d_gidx = reinterpret_cast<const int *>(base + wo[i].i);
   }
   p.segdev = reinterpret_cast<SegDev *>(base + o_segdev);
@@ -376,9 +375,8 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
   const WinLayout &wl = mode == MODE_X ? p.wx : p.ws;
   if (!wl.M || g.nlines >= (int64_t(1) << 31)) return false;
   const int Q = st ? (st->lo >= -2 && st->hi <= 2 ? 2 : 3) : (how == WIN_BATCH ? 2 : 0);
-  const int prec = p.precision == CB_FP64 ? 0 : (p.refine_iters > 0 ? 2 : 1);
-  w.k = find_win_kernel(p.R, wl.M, prec, mode, Q, wl.uniform != 0);
-  const WinKernel *wide = find_win_kernel(p.R, wl.M, prec, mode, 3, wl.uniform != 0);  // the most LDS
+  w.k = find_win_kernel(p.R, wl.M, mode, Q, wl.uniform != 0);
+  const WinKernel *wide = find_win_kernel(p.R, wl.M, mode, 3, wl.uniform != 0);  // the most LDS
   if (how == WIN_COPY) w.k = find_win_copy_kernel(wl.M, mode, wl.uniform != 0);
   if (!w.k || !wide) return false;
   WinArgs &a = w.a;
@@ -411,10 +409,7 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
   a.Lw = wl.L;
   a.Lc = wl.L;
   a.nch = 1;
-  a.refine_iters = p.refine_iters;
-  // lanes whose solution a launch gets wrong at either end of a window: D + 1
-  // per solve, and one more for each residual between two solves
-  const int halo = (p.refine_iters + 1) * (wl.D + 1) + p.refine_iters;
+  const int halo = wl.D + 1;  // lanes whose solution a launch gets wrong at either end of a window
   // equal chunks of the line's lanes with their halo, at most `most` lanes in
   // all; one for each partition where the plan was asked for several
   const int parts = p.desc.partitions > 1 ? p.desc.partitions : 0;
@@ -489,8 +484,6 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
   a.gcount = (int)wl.g.size();
   if (st) stencil_q(st, a.stc);
   else a.stc[3] = 1.0;
-  const size_t mid = (size_t)(p.n / 2) * (2 * p.R + 1);  // an interior row: every entry present
-  for (int o = 0; o < 2 * p.R + 1; ++o) a.bands[o] = p.bands[mid + o];
   return true;
 }
 

@@ -24,8 +24,8 @@ const LineKernel *find_copy_kernel(int M, int mode, bool uni) {
 
 // The same for windowed lanes.
 #define CB_WIN_COPY(M, MODE, UNI)                                                    \
-  {1, M, 0, MODE, 0, UNI, win_max_threads<MODE>(), win_planes(1, 0, false, MODE) * win_lines(MODE), \
-   (const void *)&k_win<1, M, double, false, MODE, 0, UNI, WIN_MOVE>, nullptr}
+  {1, M, MODE, 0, UNI, win_max_threads<MODE>(), win_planes(1, 0, MODE) * win_lines(MODE), \
+   (const void *)&k_win<1, M, MODE, 0, UNI, WIN_MOVE>, nullptr}
 static const WinKernel kWinCopy[] = {
     CB_WIN_COPY(8, MODE_X, true),  CB_WIN_COPY(10, MODE_X, true),  CB_WIN_COPY(12, MODE_X, true),
     CB_WIN_COPY(16, MODE_X, true), CB_WIN_COPY(20, MODE_X, true),  CB_WIN_COPY(24, MODE_X, true),

@@ -178,7 +178,7 @@ const WinKernel *win_table_r2_s(int *count);
 const WinKernel *win_table_r3_x(int *count);
 const WinKernel *win_table_r3_s(int *count);
 
-const WinKernel *find_win_kernel(int R, int M, int prec, int mode, int Q, bool uni) {
+const WinKernel *find_win_kernel(int R, int M, int mode, int Q, bool uni) {
   const WinKernel *(*const tables[])(int *) = {win_table_r1_x, win_table_r1_s, win_table_r2_x, win_table_r2_s,
                                               win_table_r3_x, win_table_r3_s};
   for (auto table : tables) {
@@ -186,7 +186,7 @@ const WinKernel *find_win_kernel(int R, int M, int prec, int mode, int Q, bool u
     const WinKernel *t = table(&cnt);
     if (t[0].R != R || t[0].mode != mode) continue;
     for (int i = 0; i < cnt; ++i)
-      if (t[i].R == R && t[i].M == M && t[i].prec == prec && t[i].mode == mode && t[i].Q == Q && t[i].uni == uni)
+      if (t[i].R == R && t[i].M == M && t[i].mode == mode && t[i].Q == Q && t[i].uni == uni)
         return &t[i];
   }
   return nullptr;

@@ -61,13 +61,12 @@ struct WinArgs {
   int pitch;                 // ... and tile words per line
   int chunk_fast;            // chunks of a line are consecutive tiles
   uint32_t ltiles;           // line tiles (chunk slowest)
-  int xcds, refine_iters;
+  int xcds;
   int nt, gcount;            // streaming loads and stores; values in g
-  const void *coef, *g;
+  const double *coef, *g;
   const int *gidx;
   int lo, hi;                // stencil by itself: its taps
   double stc[7];             // stencil coefficients for q = -3..3
-  double bands[2 * kMaxR + 1];
 };
 
 struct WgArgs {
@@ -127,7 +126,7 @@ struct LineKernel {
   const void *fn;
 };
 struct WinKernel {
-  int R, M, prec, mode, Q;   // prec: 0 FP64, 1 FP32, 2 FP32 + refinement
+  int R, M, mode, Q;
   bool uni;
   int max_threads;
   int lds;                   // LDS doubles per slot
@@ -198,7 +197,7 @@ const BatchKernel *find_batch_kernel(int R, int M, int fp32, bool uni, bool ilu,
 const WgKernel *find_wg_kernel(int R, int M, int mode, int Q, bool ilu);
 // FP32 + refinement instances of the partitioned kernels (wg_fp32.hip)
 const WgKernel *find_wg32_kernel(int R, int M, int mode, int Q, bool ilu);
-const WinKernel *find_win_kernel(int R, int M, int prec, int mode, int Q, bool uni);
+const WinKernel *find_win_kernel(int R, int M, int mode, int Q, bool uni);
 const WinKernel *find_win_copy_kernel(int M, int mode, bool uni);
 const void *stencil_kernel(int form);
 const WinKernel *find_win_stencil_kernel(int Q);  // unit-stride lines, 16-row lanes

@@ -905,6 +905,14 @@ int auto_refine_iters(const cb_plan_desc &d) {
 // one that leaves the fewest of a wavefront's rows idle (halo lanes and the
 // lanes beyond the last line count as idle).
 //
+// FP32 + refinement takes the same lanes in FP64 wherever they apply: one solve
+// bound by memory instead of two or more with a residual between them, on a
+// chip whose unpacked FP32 rate is its FP64 rate, and closer to the exact
+// solution.  Two FP32 windowed solves measured no faster along x (382 / 387
+// GDOF/s).  Sixth-order interpolation at 384^3, x / y / z 314 / 237 / 219 ->
+// 384 / 343 / 306 GDOF/s; tenth-order derivative at n = 512 (two iterations)
+// 168 / 147 / 141 -> 370 / 335 / 287.
+//
 // Strided lines (a workgroup holds the lanes of 8-32 pairs of adjacent lines):
 // the fewest rows per lane that keep a line within 32 lanes, so that 16 pairs
 // make 512 threads and two workgroups share a compute unit.  Lanes of one size
@@ -914,18 +922,21 @@ int auto_refine_iters(const cb_plan_desc &d) {
 // 212 with 19 of 15 or 16).
 static void choose_windows(const cb_plan_desc &d, Plan &p) {
   if (d.per_row || d.rows_per_lane || d.lines_per_wg || d.block_barriers || d.x_staging || d.interior) return;
-  if (d.precision != CB_FP64) return;
+  if (d.precision == CB_FP32) return;
   const int n = d.n, R = d.r;
   const bool cyclic = d.cyclic != 0;
   const int parts = d.partitions > 1 ? d.partitions : 0;
   const double tol = std::ldexp(1.0, -57);
   auto build = [&](int M, bool ring, WinLayout &w) { return build_window(n, R, d.bands, cyclic, M, tol, ring, w); };
-  if (cyclic && (parts || !(p.segs[0].uniform && n <= 2048))) {
+  if (cyclic && (parts || d.precision != CB_FP64 || !(p.segs[0].uniform && n <= 2048))) {
     static const int exact1[] = {12, 10, 16, 8, 20, 24}, exact2[] = {12, 16, 10, 20, 24, 8}, exact3[] = {16};
     const int *exact = R == 1 ? exact1 : (R == 2 ? exact2 : exact3);
     const int count = R == 3 ? 1 : 6;
-    for (int i = 0; i < count && !p.wx.M && !parts; ++i)
-      if (n % exact[i] == 0 && n / exact[i] <= 64) build(exact[i], false, p.wx);
+    for (int full = 1; full >= 0; --full)  // wavefronts without idle lanes first
+      for (int i = 0; i < count && !p.wx.M && !parts; ++i) {
+        const int L = n / exact[i];
+        if (n % exact[i] == 0 && L <= 64 && (!full || 64 % L == 0)) build(exact[i], false, p.wx);
+      }
     double best = 0.0;
     if (!p.wx.M)
       for (int M : {16, 12, 10, 8, 20, 24}) {

@@ -115,7 +115,7 @@ struct WinLayout {
   std::vector<double> coef;                      // row[M - R][4R + 1], then z
   std::vector<double> g;
   std::vector<int> gidx;
-  const void *d_coef = nullptr, *d_g = nullptr;  // double, or float in FP32 plans
+  const double *d_coef = nullptr, *d_g = nullptr;
   const int *d_gidx = nullptr;
 };
 constexpr int win_row_size(int R) { return 4 * R + 1; }

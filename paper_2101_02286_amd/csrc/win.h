@@ -32,33 +32,23 @@ namespace cb {
 // chains of dependent operations in flight (16 rows of two lines instead of 32
 // of one, 512^3 sixth order y / z 341 / 324 -> 355 / 348 GDOF/s).  Unit-stride
 // rows one line per thread.
-typedef float flt2 __attribute__((ext_vector_type(2)));
 typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));  // any 8-byte address
-template <typename T, int NL> struct WinVec { typedef T type; };
-template <> struct WinVec<double, 2> { typedef dbl2 type; };
-template <> struct WinVec<float, 2> { typedef flt2 type; };
-__device__ __forceinline__ void win_cast(double v, float &o) { o = (float)v; }
-__device__ __forceinline__ void win_cast(float v, double &o) { o = (double)v; }
-__device__ __forceinline__ void win_cast(dbl2 v, flt2 &o) { o = __builtin_convertvector(v, flt2); }
-__device__ __forceinline__ void win_cast(flt2 v, dbl2 &o) { o = __builtin_convertvector(v, dbl2); }
+template <int NL> struct WinVec { typedef double type; };
+template <> struct WinVec<2> { typedef dbl2 type; };
 
 constexpr int win_lines(int mode) { return mode == MODE_S ? 2 : 1; }  // lines per thread
 
 // LDS planes, one value per thread and plane: the halo of Q rows per side that
-// strided rows exchange for the stencil, or of R rows for the residual, and
-// what a lane shares for the reduced system (2R).  Where both together would
-// leave one workgroup to a compute unit, the second takes the first's place
-// behind a barrier of its own.
-constexpr int win_halo_planes(int R, int Q, bool ref, int mode) {
-  const int q = mode == MODE_S ? 2 * Q : 0, r = ref ? 2 * R : 0;
-  return q > r ? q : r;
+// strided rows exchange for the stencil, and what a lane shares for the reduced
+// system (2R).  Where both together would leave one workgroup to a compute unit,
+// the second takes the first's place behind a barrier of its own.
+constexpr int win_halo_planes(int Q, int mode) { return mode == MODE_S ? 2 * Q : 0; }
+constexpr bool win_shared_planes(int R, int Q, int mode) {
+  return mode == MODE_S && win_halo_planes(Q, mode) + 2 * R >= 8;
 }
-constexpr bool win_shared_planes(int R, int Q, bool ref, int mode) {
-  return mode == MODE_S && win_halo_planes(R, Q, ref, mode) + 2 * R >= 8;
-}
-constexpr int win_planes(int R, int Q, bool ref, int mode) {
-  const int h = win_halo_planes(R, Q, ref, mode);
-  return win_shared_planes(R, Q, ref, mode) ? (h > 2 * R ? h : 2 * R) : h + 2 * R;
+constexpr int win_planes(int R, int Q, int mode) {
+  const int h = win_halo_planes(Q, mode);
+  return win_shared_planes(R, Q, mode) ? (h > 2 * R ? h : 2 * R) : h + 2 * R;
 }
 
 // Position of a thread: lane l of the Lw its line (or pair of lines) has in the
@@ -101,15 +91,15 @@ struct WinPos {
 // reduced system's inverse, and x~_{l+1} by the same window one lane on (a
 // second exchange would cost a barrier).  ct: c and t of Eq. (21).  g: one row
 // for the whole wavefront, read through the scalar cache ahead of the barrier.
-template <int R, int D, typename T, typename V>
-__device__ __forceinline__ void win_reduce(const T *g, const WinPos &p, V *ex, const V (&ct)[2 * R], V (&xt)[R],
+template <int R, int D, typename V>
+__device__ __forceinline__ void win_reduce(const double *g, const WinPos &p, V *ex, const V (&ct)[2 * R], V (&xt)[R],
                                            V (&xn)[R]) {
-  T gm[(2 * D + 1) * R * R];
+  double gm[(2 * D + 1) * R * R];
 #pragma unroll
   for (int i = 0; i < (2 * D + 1) * R * R; ++i) gm[i] = cld(g + i);
   p.publish(ex, ct, D + 1);
 #pragma unroll
-  for (int a = 0; a < R; ++a) xt[a] = xn[a] = (V)(T)0;
+  for (int a = 0; a < R; ++a) xt[a] = xn[a] = (V)0.0;
 #pragma unroll
   for (int d = -D; d <= D + 1; ++d) {
 #pragma unroll
@@ -127,15 +117,15 @@ __device__ __forceinline__ void win_reduce(const T *g, const WinPos &p, V *ex, c
 }
 // The same for lanes that read different rows (gn: the next lane's), and for
 // wide windows.  g, gn: in LDS, or uniform.
-template <int R, typename T, typename V>
-__device__ __forceinline__ void win_reduce_any(const T *g, const T *gn, const WinPos &p, V *ex,
+template <int R, typename V>
+__device__ __forceinline__ void win_reduce_any(const double *g, const double *gn, const WinPos &p, V *ex,
                                                const V (&ct)[2 * R], V (&xt)[R], V (&xn)[R]) {
   p.publish(ex, ct, p.D + 1);
 #pragma unroll
-  for (int a = 0; a < R; ++a) xt[a] = xn[a] = (V)(T)0;
+  for (int a = 0; a < R; ++a) xt[a] = xn[a] = (V)0.0;
   const int at = p.at - p.D * p.step;
   auto value = [&](int d, int b) { return ex[b * p.NS + at + d * p.step] - ex[(R + b) * p.NS + at + (d - 1) * p.step]; };
-  auto add = [&](V(&x)[R], const T *row, V v, int b) {
+  auto add = [&](V(&x)[R], const double *row, V v, int b) {
 #pragma unroll
     for (int a = 0; a < R; ++a) x[a] += row[a * R + b] * v;
   };
@@ -156,12 +146,12 @@ __device__ __forceinline__ void win_reduce_any(const T *g, const T *gn, const Wi
 // Solve the lane's rows v (b on entry, x on exit).  sh: the lane holds M - 1
 // rows.  last: the last lane of an acyclic line.  gi, gin: the lane's and the
 // next lane's row of the window table g, whose copy in LDS is gl.
-template <int R, int M, typename T, typename V, bool UNI>
-__device__ __forceinline__ void win_solve(V (&v)[M], const T *cf, const T *g, const T *gl, int gi, int gin, const WinPos &p, V *ex,
+template <int R, int M, typename V, bool UNI>
+__device__ __forceinline__ void win_solve(V (&v)[M], const double *cf, const double *g, const double *gl, int gi, int gin, const WinPos &p, V *ex,
                                           bool sh, bool last) {
   constexpr int N = M - R, RW = win_row_size(R), RR = R * R;
   const int D = p.D;
-  const V zero = (V)(T)0;
+  const V zero = (V)0.0;
   // z = L^{-1} b on the interior rows
 #pragma unroll
   for (int j = 1; j < N; ++j)
@@ -187,7 +177,7 @@ __device__ __forceinline__ void win_solve(V (&v)[M], const T *cf, const T *g, co
       V acc = zero;
 #pragma unroll
       for (int i = 0; i < R; ++i) {
-        const T z0 = cld(cf + N * RW + a * R + i);
+        const double z0 = cld(cf + N * RW + a * R + i);
         acc += (UNI ? z0 : (sh ? cld(cf + N * RW + RR + a * R + i) : z0)) * zl[i];
       }
       ct[R + a] = (!UNI && last) ? zero : acc;
@@ -195,18 +185,18 @@ __device__ __forceinline__ void win_solve(V (&v)[M], const T *cf, const T *g, co
   }
   // x~: most wavefronts hold lanes that share one window row
   const int gu = UNI ? 0 : __builtin_amdgcn_readfirstlane(gi);
-  const T *gw = g + (size_t)gu * ((2 * D + 1) * RR);
+  const double *gw = g + (size_t)gu * ((2 * D + 1) * RR);
   constexpr int DF = M >= 24 ? 3 : (R == 1 ? 6 : 4);  // unrolled windows
   if (D <= DF && (UNI || __all(gi == gu && gin == gu))) {
-    if (D == 1) win_reduce<R, 1, T, V>(gw, p, ex, ct, xt, xr);
-    else if (D == 2) win_reduce<R, 2, T, V>(gw, p, ex, ct, xt, xr);
-    else if (D == 3) win_reduce<R, 3, T, V>(gw, p, ex, ct, xt, xr);
-    else if (DF >= 4 && D == 4) win_reduce<R, DF >= 4 ? 4 : 1, T, V>(gw, p, ex, ct, xt, xr);
-    else if (DF >= 5 && D == 5) win_reduce<R, DF >= 5 ? 5 : 1, T, V>(gw, p, ex, ct, xt, xr);
-    else if (DF >= 6) win_reduce<R, DF >= 6 ? 6 : 1, T, V>(gw, p, ex, ct, xt, xr);
+    if (D == 1) win_reduce<R, 1, V>(gw, p, ex, ct, xt, xr);
+    else if (D == 2) win_reduce<R, 2, V>(gw, p, ex, ct, xt, xr);
+    else if (D == 3) win_reduce<R, 3, V>(gw, p, ex, ct, xt, xr);
+    else if (DF >= 4 && D == 4) win_reduce<R, DF >= 4 ? 4 : 1, V>(gw, p, ex, ct, xt, xr);
+    else if (DF >= 5 && D == 5) win_reduce<R, DF >= 5 ? 5 : 1, V>(gw, p, ex, ct, xt, xr);
+    else if (DF >= 6) win_reduce<R, DF >= 6 ? 6 : 1, V>(gw, p, ex, ct, xt, xr);
   } else {
-    const T *gs = UNI ? g : gl;
-    win_reduce_any<R, T, V>(gs + gi * ((2 * D + 1) * RR), gs + gin * ((2 * D + 1) * RR), p, ex, ct, xt, xr);
+    const double *gs = UNI ? g : gl;
+    win_reduce_any<R, V>(gs + gi * ((2 * D + 1) * RR), gs + gin * ((2 * D + 1) * RR), p, ex, ct, xt, xr);
   }
 #pragma unroll
   for (int a = 0; a < R; ++a) xn[a] = (!UNI && last) ? zero : xr[a];
@@ -285,12 +275,11 @@ enum { WIN_SOLVE = 0, WIN_MOVE = 1, WIN_STENCIL = 2 };
 
 // One tile: the lanes of W lines (pairs of lines), or of one run of lanes
 // (chunk) of each of them with H halo lanes on either side.
-template <int R, int M, typename T, bool REF, int MODE, int Q, bool UNI, int OP>
+template <int R, int M, int MODE, int Q, bool UNI, int OP>
 __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double *smem) {
   constexpr int QQ = Q > 0 ? Q : 1;
   constexpr int KT = Q > 0 ? M + 2 : M;  // tile rows a lane loads (a window's halo needs one or two more)
-  typedef typename WinVec<double, win_lines(MODE)>::type VD;
-  typedef typename WinVec<T, win_lines(MODE)>::type V;
+  typedef typename WinVec<win_lines(MODE)>::type VD;
   const int tid = threadIdx.x;
   WinPos p;
   p.Lw = a.Lw;
@@ -364,7 +353,7 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
   auto at = [](int e) { return e + (int)((uint32_t)(e + M) / (uint32_t)M) - 1; };
   constexpr int QP = (Q + 1) & ~1;  // halo rows beyond the window's lanes, kept even
   if constexpr (MODE == MODE_X) {
-    tb = smem + (size_t)win_planes(R, Q, REF, MODE) * p.NS + (size_t)li * a.pitch + QP + 2;
+    tb = smem + (size_t)win_planes(R, Q, MODE) * p.NS + (size_t)li * a.pitch + QP + 2;
     len = a.n;
     if (a.ring) {
       r0 = ((int)ch * a.Lc - H) * M;
@@ -434,9 +423,9 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
   }
   // lanes of two sizes read different rows of the window table: copied to LDS
   // (visible after the next exchange)
-  T *gl = reinterpret_cast<T *>(smem + (size_t)win_planes(R, Q, REF, MODE) * win_lines(MODE) * p.NS);
+  double *gl = reinterpret_cast<double *>(smem + (size_t)win_planes(R, Q, MODE) * win_lines(MODE) * p.NS);
   if (!UNI && OP == WIN_SOLVE) {
-    const T *gw = static_cast<const T *>(a.g);
+    const double *gw = static_cast<const double *>(a.g);
     for (int i = tid; i < a.gcount; i += blockDim.x) gl[i] = gw[i];
   }
   if (Q > 0 && OP != WIN_MOVE) {  // fused right-hand-side stencil (Eqs. (1)-(2)), periodic
@@ -475,64 +464,15 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
     for (int k = 0; k < M; ++k) b64[k] = bb[k];
   }
   if (OP == WIN_SOLVE) {
-    const T *cf = static_cast<const T *>(a.coef);
-    const T *gw = static_cast<const T *>(a.g);
+    const double *cf = static_cast<const double *>(a.coef);
+    const double *gw = static_cast<const double *>(a.g);
     const int gi = UNI ? 0 : a.gidx[g], gin = UNI ? 0 : a.gidx[g + 1 < a.L ? g + 1 : 0];
     const bool last = !UNI && a.acyclic && g == a.L - 1;
-    constexpr bool shared = win_shared_planes(R, Q, REF, MODE);
-    constexpr int HP = win_halo_planes(R, Q, REF, MODE) * win_lines(MODE);
-    V *ex = reinterpret_cast<V *>(smem + (shared ? 0 : (size_t)HP * p.NS));
-    auto solve = [&](V(&v)[M], bool halo) {
-      if (shared && halo) p.sync();  // the halo has been read
-      win_solve<R, M, T, V, UNI>(v, cf, gw, gl, gi, gin, p, ex, sh, last);
-    };
-    if constexpr (sizeof(T) == 8) {
-      solve(b64, Q > 0);
-    } else if constexpr (!REF) {
-      V v[M];
-#pragma unroll
-      for (int k = 0; k < M; ++k) win_cast(b64[k], v[k]);
-      solve(v, Q > 0);
-#pragma unroll
-      for (int k = 0; k < M; ++k) win_cast(v[k], b64[k]);
-    } else {
-      // FP32 reduction with FP64 residual refinement: x <- x + A32^{-1}(b - A x)
-      const bool first = a.acyclic && g == 0;
-      double x64[M];
-      V v[M];
-#pragma unroll
-      for (int k = 0; k < M; ++k) win_cast(b64[k], v[k]);
-      solve(v, Q > 0);
-#pragma unroll
-      for (int k = 0; k < M; ++k) win_cast(v[k], x64[k]);
-      for (int it = 0; it < a.refine_iters; ++it) {
-        VD xp[R], xn[R], tail[R + 1];
-        if (shared) p.sync();  // the window has been read
-        win_halo<R, M, UNI, VD>(x64, sh, p, reinterpret_cast<VD *>(smem), xp, xn);
-#pragma unroll
-        for (int i = 0; i < R; ++i) {
-          xp[i] = first ? zero : xp[i];
-          xn[i] = last ? zero : xn[i];
-        }
-        win_tail<R, M, UNI, VD>(x64, xn, sh, tail);
-#pragma unroll
-        for (int k = 0; k < M; ++k) {
-          VD r = b64[k];
-#pragma unroll
-          for (int o = -R; o <= R; ++o) r -= a.bands[o + R] * win_at<R, M, VD>(x64, xp, tail, k + o);
-          win_cast((!UNI && k == M - 1 && sh) ? zero : r, v[k]);
-        }
-        solve(v, true);
-#pragma unroll
-        for (int k = 0; k < M; ++k) {
-          VD d;
-          win_cast(v[k], d);
-          x64[k] += d;
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < M; ++k) b64[k] = x64[k];
-    }
+    constexpr bool shared = win_shared_planes(R, Q, MODE);
+    constexpr int HP = win_halo_planes(Q, MODE) * win_lines(MODE);
+    VD *ex = reinterpret_cast<VD *>(smem + (shared ? 0 : (size_t)HP * p.NS));
+    if (shared && Q > 0) p.sync();  // the halo has been read
+    win_solve<R, M, VD, UNI>(b64, cf, gw, gl, gi, gin, p, ex, sh, last);
   }
   if constexpr (MODE == MODE_X) {
     if (OP != WIN_SOLVE) p.sync();  // (the solve's exchange lies in between)
@@ -587,7 +527,7 @@ constexpr int win_max_threads() {
   return MODE == MODE_X ? 256 : 1024;
 }
 
-template <int R, int M, typename T, bool REF, int MODE, int Q, bool UNI, int OP = WIN_SOLVE>
+template <int R, int M, int MODE, int Q, bool UNI, int OP = WIN_SOLVE>
 __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win(const WinArgs a) {
   extern __shared__ __align__(16) double smem[];
   uint32_t tile = blockIdx.x;
@@ -596,13 +536,13 @@ __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win(const WinA
     const uint32_t j = tile % X, s = tile / X;
     tile = j * q + (j < rem ? j : rem) + s;
   }
-  win_tile<R, M, T, REF, MODE, Q, UNI, OP>(a, tile, smem);
+  win_tile<R, M, MODE, Q, UNI, OP>(a, tile, smem);
 }
 
 // Batched launch over the tiles of many items of one instance, as k_batched.
 // Wavefronts beyond an item's own workgroup size leave at once (a barrier
 // counts the wavefronts that remain) or, in the persistent form, idle.
-template <int R, int M, typename T, bool REF, int MODE, int Q, bool UNI>
+template <int R, int M, int MODE, int Q, bool UNI>
 __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win_batched(BatchHdr *hdr,
                                                                              const WinItemDev *__restrict__ items,
                                                                              int per_tile) {
@@ -629,7 +569,7 @@ __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win_batched(Ba
       const uint32_t X = (uint32_t)it.a.xcds, q = G / X, rem = G % X, j = local % X, s = local / X;
       local = j * q + (j < rem ? j : rem) + s;
     }
-    win_tile<R, M, T, REF, MODE, Q, UNI, WIN_SOLVE>(it.a, local, smem);
+    win_tile<R, M, MODE, Q, UNI, WIN_SOLVE>(it.a, local, smem);
     return;
   }
   for (;;) {
@@ -640,7 +580,7 @@ __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win_batched(Ba
     __syncthreads();
     if (t >= total) break;
     const WinItemDev &it = items[item_of(t)];
-    win_tile<R, M, T, REF, MODE, Q, UNI, WIN_SOLVE>(it.a, (uint32_t)(t - it.tile_begin), smem);
+    win_tile<R, M, MODE, Q, UNI, WIN_SOLVE>(it.a, (uint32_t)(t - it.tile_begin), smem);
     __syncthreads();
   }
   if (threadIdx.x == 0) {
@@ -654,25 +594,25 @@ __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win_batched(Ba
   }
 }
 
-template <int R, int M, typename T, bool REF, int MODE, int Q, bool UNI>
+template <int R, int M, int MODE, int Q, bool UNI>
 const void *win_batched() {
-  if constexpr (Q > 0) return (const void *)&k_win_batched<R, M, T, REF, MODE, Q, UNI>;
+  if constexpr (Q > 0) return (const void *)&k_win_batched<R, M, MODE, Q, UNI>;
   else return nullptr;
 }
 
-#define CB_WIN_INST(R, M, T, REF, MODE, Q, UNI)                                                     \
-  {R, M, sizeof(T) == 8 ? 0 : (REF ? 2 : 1), MODE, Q, UNI, win_max_threads<MODE>(),                  \
-   win_planes(R, Q, REF, MODE) * win_lines(MODE), (const void *)&k_win<R, M, T, REF, MODE, Q, UNI>, \
-   win_batched<R, M, T, REF, MODE, Q, UNI>()}
-#define CB_WIN_U(R, M, T, REF, MODE, U) \
-  CB_WIN_INST(R, M, T, REF, MODE, 0, U), CB_WIN_INST(R, M, T, REF, MODE, 2, U), CB_WIN_INST(R, M, T, REF, MODE, 3, U)
-#define CB_WIN_X(R, M, T, REF) CB_WIN_U(R, M, T, REF, MODE_X, true)
+#define CB_WIN_INST(R, M, MODE, Q, UNI)                                                     \
+  {R, M, MODE, Q, UNI, win_max_threads<MODE>(),                  \
+   win_planes(R, Q, MODE) * win_lines(MODE), (const void *)&k_win<R, M, MODE, Q, UNI>, \
+   win_batched<R, M, MODE, Q, UNI>()}
+#define CB_WIN_U(R, M, MODE, U) \
+  CB_WIN_INST(R, M, MODE, 0, U), CB_WIN_INST(R, M, MODE, 2, U), CB_WIN_INST(R, M, MODE, 3, U)
+#define CB_WIN_X(R, M) CB_WIN_U(R, M, MODE_X, true)
 // the stencil by itself on unit-stride lines, in lanes of 16 rows
 #define CB_WIN_STENCIL(Q)                                                                              \
   WinKernel {                                                                                          \
-    1, 16, 0, MODE_X, Q, true, win_max_threads<MODE_X>(), win_planes(1, Q, false, MODE_X),             \
-        (const void *)&k_win<1, 16, double, false, MODE_X, Q, true, WIN_STENCIL>, nullptr              \
+    1, 16, MODE_X, Q, true, win_max_threads<MODE_X>(), win_planes(1, Q, MODE_X),             \
+        (const void *)&k_win<1, 16, MODE_X, Q, true, WIN_STENCIL>, nullptr              \
   }
-#define CB_WIN_S(R, M, T, REF) CB_WIN_U(R, M, T, REF, MODE_S, false), CB_WIN_U(R, M, T, REF, MODE_S, true)
+#define CB_WIN_S(R, M) CB_WIN_U(R, M, MODE_S, false), CB_WIN_U(R, M, MODE_S, true)
 
 }  // namespace cb

@@ -3,9 +3,9 @@
 
 namespace cb {
 
-static const WinKernel kTable[] = {CB_WIN_S(1, 8, double, false),
-                                   CB_WIN_S(1, 12, double, false),
-                                   CB_WIN_S(1, 16, double, false)};
+static const WinKernel kTable[] = {CB_WIN_S(1, 8),
+                                   CB_WIN_S(1, 12),
+                                   CB_WIN_S(1, 16)};
 
 const WinKernel *win_table_r1_s(int *count) {
   *count = (int)(sizeof(kTable) / sizeof(kTable[0]));

@@ -3,12 +3,12 @@
 
 namespace cb {
 
-static const WinKernel kTable[] = {CB_WIN_X(1, 8, double, false),
-                                   CB_WIN_X(1, 10, double, false),
-                                   CB_WIN_X(1, 12, double, false),
-                                   CB_WIN_X(1, 16, double, false),
-                                   CB_WIN_X(1, 20, double, false),
-                                   CB_WIN_X(1, 24, double, false)};
+static const WinKernel kTable[] = {CB_WIN_X(1, 8),
+                                   CB_WIN_X(1, 10),
+                                   CB_WIN_X(1, 12),
+                                   CB_WIN_X(1, 16),
+                                   CB_WIN_X(1, 20),
+                                   CB_WIN_X(1, 24)};
 
 const WinKernel *win_table_r1_x(int *count) {
   *count = (int)(sizeof(kTable) / sizeof(kTable[0]));

@@ -3,7 +3,7 @@
 
 namespace cb {
 
-static const WinKernel kTable[] = {CB_WIN_S(3, 16, double, false)};
+static const WinKernel kTable[] = {CB_WIN_S(3, 16)};
 
 const WinKernel *win_table_r3_s(int *count) {
   *count = (int)(sizeof(kTable) / sizeof(kTable[0]));

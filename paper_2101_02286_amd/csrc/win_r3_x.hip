@@ -3,7 +3,7 @@
 
 namespace cb {
 
-static const WinKernel kTable[] = {CB_WIN_X(3, 16, double, false)};
+static const WinKernel kTable[] = {CB_WIN_X(3, 16)};
 
 const WinKernel *win_table_r3_x(int *count) {
   *count = (int)(sizeof(kTable) / sizeof(kTable[0]));

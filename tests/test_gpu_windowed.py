@@ -84,3 +84,18 @@ def test_partitions(gpu, axis, n, P):
     for band in ("tri", "penta"):
         x = cb.solve(cb.Plan(BANDS[band], n, partitions=P), b.to(gpu), axis).cpu().numpy()
         assert relerr(x, oracle.solve_axis(b.numpy(), axis, BANDS[band])) <= TOL
+
+
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("band", ["tri", "penta", "hept"])
+@pytest.mark.parametrize("n", [64, 96, 128, 192, 320, 384, 512, 613, 1024, 2048])
+def test_refined_plans(gpu, axis, band, n):
+    """FP32 + refinement: solves to the FP64 bound, whatever count is asked for."""
+    shape = grid(axis, n, (35, 3))
+    f = synth.random_uniform(shape, seed=n)
+    lo, c = STENCILS[band]
+    ref = oracle.apply_axis(f.numpy(), axis, BANDS[band], lo, c)
+    for iters in (0, 3):
+        plan = cb.Plan(BANDS[band], n, precision="fp32_refine", refine_iters=iters)
+        x = cb.apply_derivative(plan, cb.Stencil(lo, c), f.to(gpu), axis).cpu().numpy()
+        assert relerr(x, ref) <= TOL

@@ -39,6 +39,10 @@ WINDOWED = """
 1 1700 1 33 1 0 0 0 0 0 0 0
 1 2048 0 2 2 0 1 0 0 0 4 0
 2 2048 1 17 2 0 1 0 0 0 8 1
+1 64 0 5 3 0 1 2 2 0 0 0
+1 384 0 3 2 1 1 0 2 1 0 0
+2 128 0 5 1 0 1 3 2 0 0 1
+1 200 2 9 2 0 1 0 2 1 0 0
 0 32 0 5 3 0 1 2 0 0 0 0
 0 33 0 7 2 1 1 3 0 0 0 0
 0 48 0 3 3 0 1 2 0 0 0 0
@@ -46,11 +50,12 @@ WINDOWED = """
 0 1025 0 3 2 1 1 1 0 0 0 0
 0 2071 0 2 2 0 1 3 0 0 0 0
 """
-# in place in several chunks, and unit-stride acyclic lines: the general kernels
+# in place in several chunks, unit-stride acyclic lines, plain FP32: the general kernels
 GENERAL = """
 1 1700 1 4 2 0 1 0 0 1 0 0
 1 1900 0 2 2 0 1 0 0 1 0 0
 1 300 0 2 2 0 0 0 0 0 0 0
+1 300 1 4 2 0 1 2 1 0 0 0
 """
 
 

@@ -26,14 +26,14 @@ alignas(256) double smem[163840 / sizeof(double)];
 
 // the instances that the cases use
 static const WinKernel kTable[] = {
-    CB_WIN_X(1, 8, double, false), CB_WIN_X(1, 10, double, false), CB_WIN_X(1, 12, double, false),
-    CB_WIN_X(1, 16, double, false), CB_WIN_X(2, 16, double, false), CB_WIN_X(2, 20, double, false),
-    CB_WIN_X(2, 24, double, false), CB_WIN_S(1, 8, double, false),  CB_WIN_S(2, 8, double, false),
-    CB_WIN_S(2, 12, double, false), CB_WIN_S(2, 16, double, false), CB_WIN_S(1, 16, double, false),
+    CB_WIN_X(1, 8), CB_WIN_X(1, 10), CB_WIN_X(1, 12),
+    CB_WIN_X(1, 16), CB_WIN_X(2, 16), CB_WIN_X(2, 20),
+    CB_WIN_X(2, 24), CB_WIN_S(1, 8),  CB_WIN_S(2, 8),
+    CB_WIN_S(2, 12), CB_WIN_S(2, 16), CB_WIN_S(1, 16),
 };
-const WinKernel *find_win_kernel(int R, int M, int prec, int mode, int Q, bool uni) {
+const WinKernel *find_win_kernel(int R, int M, int mode, int Q, bool uni) {
   for (const auto &k : kTable)
-    if (k.R == R && k.M == M && k.prec == prec && k.mode == mode && k.Q == Q && k.uni == uni) return &k;
+    if (k.R == R && k.M == M && k.mode == mode && k.Q == Q && k.uni == uni) return &k;
   return nullptr;
 }
 // anything else is named but not run
