@@ -16,7 +16,8 @@ LIB = os.path.join(PKG, "libcb.so")
 SOURCES = ["kernels.hip", "lines_m4.hip", "lines_m6.hip", "lines_m8.hip", "lines_m12.hip", "lines_m16.hip",
            "lines_m32.hip", "lines_r3_m8.hip", "lines_r3_m16.hip", "copy_lines.hip", "wg_fp32_m8.hip", "wg_fp32_m16.hip",
            "win_r1_x.hip", "win_r1_s.hip", "win_r2_x.hip", "win_r2_s.hip",
-           "win_r3_x.hip", "win_r3_s.hip", "noalloc.hip",
+           "win_r3_x.hip", "win_r3_s.hip",
+           "win_rows_r1.hip", "win_rows_r2.hip", "win_rows_r3.hip", "noalloc.hip",
            "plan.cpp", "api.cpp"]
 ARCH = "gfx950"
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "-Wall", "--offload-arch=" + ARCH,

@@ -31,11 +31,12 @@ struct BatchLaunch {
   int threads;
   int64_t tiles;
 };
-// An item whose plan splits lines over P > 1 workgroup partitions: it runs
-// as its own phase launches, with its partition scratch in the workspace.
-struct WgItem {
+// An item with launches of its own: lines split over P > 1 workgroup
+// partitions (its phase launches, with its partition scratch in the workspace),
+// or lanes with coefficients of their own (cb_solve's launch).
+struct OwnItem {
   cb_plan_t plan;
-  const Plan *wp;  // what runs: the plan (P > 1) or its partitioned strided copy
+  const Plan *wp;  // partitioned: the plan (P > 1) or its partitioned strided copy; else null
   cb_grid grid;
   int axis;
   const double *in;
@@ -48,7 +49,7 @@ struct WgItem {
 // from, and the event recorded on the build stream after that upload.
 struct BatchState {
   std::vector<BatchLaunch> launches;
-  std::vector<WgItem> wg_items;
+  std::vector<OwnItem> own;
   hipStream_t stream = nullptr;
   hipEvent_t copied = nullptr;
   char *pinned = nullptr;
@@ -370,13 +371,16 @@ struct WinLaunch {
 // arithmetic; whether a call runs this way does not depend on it.
 enum WinHow { WIN_SINGLE, WIN_BATCH, WIN_COPY };
 bool win_config(const Plan &p, const Geo &g, const double *in, double *out, const cb_stencil *st, WinHow how,
-                WinLaunch &w) {
+                WinLaunch &w, bool small = false) {
   const int mode = g.rs == 1 ? MODE_X : MODE_S;
   const WinLayout &wl = mode == MODE_X ? p.wx : p.ws;
-  if (!wl.M || g.nlines >= (int64_t(1) << 31)) return false;
+  if (!wl.M || g.nlines >= (int64_t(1) << 31) || (wl.rows && how == WIN_BATCH)) return false;
   const int Q = st ? (st->lo >= -2 && st->hi <= 2 ? 2 : 3) : (how == WIN_BATCH ? 2 : 0);
-  w.k = find_win_kernel(p.R, wl.M, mode, Q, wl.uniform != 0);
-  const WinKernel *wide = find_win_kernel(p.R, wl.M, mode, 3, wl.uniform != 0);  // the most LDS
+  auto find = [&](int q) {
+    return wl.rows ? find_win_rows_kernel(p.R, wl.M, mode, q) : find_win_kernel(p.R, wl.M, mode, q, wl.uniform != 0);
+  };
+  w.k = find(Q);
+  const WinKernel *wide = wl.rows ? w.k : find(3);  // the most LDS
   if (how == WIN_COPY) w.k = find_win_copy_kernel(wl.M, mode, wl.uniform != 0);
   if (!w.k || !wide) return false;
   WinArgs &a = w.a;
@@ -431,10 +435,11 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
                      (uintptr_t)in % 128 == 0 && (uintptr_t)out % 128 == 0;
   if (mode == MODE_X) {
     const int QP = (Q + 1) & ~1;
-    if (parts || wl.L > 64 || wl.L * wl.M != a.n) {
+    if (!wl.rows && (parts || wl.L > 64 || wl.L * wl.M != a.n)) {
       if (!split(64) || a.n < (halo + 1) * wl.M + 4) return false;
     }
     int waves = p.R == 1 ? 4 : 1;  // (wider bands: one measured 2-10 % faster, tridiagonal ones four)
+    if (wl.rows) waves = p.R == 1 && a.Lw > 32 && !small ? 8 : 4;
     w.threads = 64 * waves;
     a.lpw = 64 / a.Lw;
     a.linv = (65536 + a.Lw - 1) / a.Lw;
@@ -454,6 +459,8 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
     int W = wl.L * 32 <= (whole ? 256 : 1024) ? 32 : 16;
     if (!whole && wl.M == 8 && wl.L > 12) W = 16;
     if (chunks) W = !whole && p.R == 1 && !parts ? 32 : 16;
+    // (coefficients in LDS: 32 pairs while two workgroups fit a compute unit)
+    if (wl.rows) W = wl.L * 32 <= (p.R == 3 ? 1024 : 512) && !small ? 32 : 16;
     if (chunks) {
       if (!split(parts ? 1024 / W : 32) || a.Lw > wl.L) return false;
     }
@@ -467,17 +474,28 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
     a.chunk_fast = whole ? 1 : 0;
   }
   auto lds_of = [&](const WinKernel *k) {
-    return ((size_t)k->lds * a.W * (a.Lw + 2 * a.D + 2) + (size_t)a.W * a.pitch + (wl.uniform ? 0 : wl.g.size())) *
-           sizeof(double);
+    return ((size_t)k->lds * a.W * (a.Lw + 2 * a.D + 2) + (size_t)a.W * (wl.rows ? 2 : 1) * a.pitch + (wl.uniform ? 0 : wl.g.size()) +
+            (wl.rows ? wl.coef.size() : 0)) * sizeof(double);
   };
   w.lds = lds_of(w.k);
+  if (wl.rows && !small && lds_of(wide) + 64 > lds_cap()) return win_config(p, g, in, out, st, how, w, true);
   if (w.threads > w.k->max_threads || lds_of(wide) + 64 > lds_cap()) return false;
-  const int64_t ltiles = (a.nlines + a.W - 1) / a.W;
+  const int per = a.W * (wl.rows && mode == MODE_X && how != WIN_COPY ? 2 : 1);  // lines, or pairs of strided ones
+  const int64_t ltiles = (a.nlines + per - 1) / per;
   w.blocks = ltiles * a.nch;
   if (w.blocks > 0x7fffffff) return false;
   a.ltiles = (uint32_t)ltiles;
   // (chunks of one line, or of neighbouring ones, on one XCD share its L2)
   a.xcds = mode == MODE_S && a.nch > 1 && p.desc.tile_order != 1 ? xcd_count() : tile_xcds(p, mode, 2 * a.W, g);
+  a.run = 1;
+  if (wl.rows && how != WIN_COPY) {
+    // several tiles per workgroup where the copy of the lanes' coefficients
+    // weighs: unit-stride lines of many lanes or r = 3 (n = 701 pentadiagonal
+    // 117 -> 140, 512 181 -> 197 GDOF/s; 300 196 -> 176; strided 301 -> 291)
+    const bool several = mode == MODE_X && (p.R == 3 || (a.Lw >= 32 && w.threads == 256));
+    a.run = several ? (int)std::min<int64_t>(3, std::max<int64_t>(1, ltiles / 1024)) : 1;
+    w.blocks = (ltiles + a.run - 1) / a.run;
+  }
   a.coef = wl.d_coef;
   a.g = wl.d_g;
   a.gidx = wl.d_gidx;
@@ -1076,7 +1094,7 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
   if (!workspace || workspace_bytes < need)
     return fail(CB_ERR_INVALID_ARG, "cb_batch_build: workspace missing or too small (needs " + std::to_string(need) +
                                         " bytes: cb_batch_workspace_bytes)");
-  std::vector<WgItem> wg_items;
+  std::vector<OwnItem> own;
   size_t sc_next = align256(batch_items_offset((size_t)n_items) + (size_t)n_items * sizeof(BatchItemDev));
   struct Cls {
     const void *fn;
@@ -1122,8 +1140,11 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
       cls[c].members.push_back(i);
       continue;
     }
-    if (const Plan *wp = batch_wg_plan(p, g)) {  // its own phase launches, scratch in the workspace
-      WgItem w;
+    const bool rows = win_config(p, g, it.in, it.out, it.stencil, WIN_SINGLE, w) && !w.k->batch_fn &&
+                      (g.rs == 1 ? p.wx : p.ws).rows;
+    const Plan *wp = rows ? nullptr : batch_wg_plan(p, g);
+    if (rows || wp) {  // its own launches, scratch in the workspace
+      OwnItem w;
       w.plan = it.plan;
       w.wp = wp;
       w.grid = it.grid;
@@ -1132,10 +1153,10 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
       w.out = it.out;
       w.has_stencil = it.stencil != nullptr;
       if (it.stencil) w.stencil = *it.stencil;
-      w.sc_bytes = wg_scratch_bytes(*wp, g.nlines);
+      w.sc_bytes = wp ? wg_scratch_bytes(*wp, g.nlines) : 0;
       w.sc_off = sc_next;
       sc_next += align256(w.sc_bytes);
-      wg_items.push_back(w);
+      own.push_back(w);
       continue;
     }
     // the plan's lane layout for this item's row stride, as a single launch uses
@@ -1319,28 +1340,28 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
   if (e == hipSuccess) e = hipEventRecord(bs.copied, st);
   if (e != hipSuccess) {
     bs.launches.clear();
-    bs.wg_items.clear();
+    bs.own.clear();
     return hip_fail(e, "cb_batch_build: copy");
   }
   bs.stream = st;
   bs.launches = std::move(launches);
-  bs.wg_items = std::move(wg_items);
+  bs.own = std::move(own);
   return CB_OK;
 }
 
 cb_status cb_batch_launch(void *workspace, int32_t max_ctas, void *stream) {
   if (!workspace) return fail(CB_ERR_INVALID_ARG, "cb_batch_launch: workspace is NULL");
   std::vector<BatchLaunch> ls;
-  std::vector<WgItem> wgs;
+  std::vector<OwnItem> own;
   hipStream_t built_on = nullptr;
   hipEvent_t copied = nullptr;
   {
     std::lock_guard<std::mutex> lk(g_batch_mu);
     auto itr = g_batch.find(workspace);
-    if (itr == g_batch.end() || (itr->second.launches.empty() && itr->second.wg_items.empty()))
+    if (itr == g_batch.end() || (itr->second.launches.empty() && itr->second.own.empty()))
       return fail(CB_ERR_INVALID_ARG, "cb_batch_launch: workspace was not built");
     ls = itr->second.launches;
-    wgs = itr->second.wg_items;
+    own = itr->second.own;
     built_on = itr->second.stream;
     copied = itr->second.copied;
   }
@@ -1389,15 +1410,16 @@ cb_status cb_batch_launch(void *workspace, int32_t max_ctas, void *stream) {
     e = hipLaunchKernel(l.fn, dim3(ctas), dim3(l.threads), args, l.lds, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "cb_batch_launch: kernel launch");
   }
-  // items split over workgroup partitions: their phase launches, with the
-  // partition scratch in the workspace (no allocation, so capturable)
-  for (const WgItem &w : wgs) {
+  // items with launches of their own (partition scratch in the workspace: no
+  // allocation, so capturable)
+  for (const OwnItem &w : own) {
     Geo g;
     cb_status s = geometry(&w.grid, w.axis, g);
     if (s) return s;
     if (g.nlines == 0) continue;
     const FixedScratch fs{static_cast<char *>(workspace) + w.sc_off, w.sc_bytes};
-    s = launch_wg(*w.wp, g, w.in, w.out, w.has_stencil ? &w.stencil : nullptr, static_cast<hipStream_t>(stream), &fs);
+    const cb_stencil *st = w.has_stencil ? &w.stencil : nullptr;
+    s = w.wp ? launch_wg(*w.wp, g, w.in, w.out, st, ls_stream, &fs) : launch(w.plan->p, g, w.in, w.out, st, ls_stream, nullptr);
     if (s) return s;
   }
   return CB_OK;

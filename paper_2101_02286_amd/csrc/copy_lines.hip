@@ -28,7 +28,8 @@ const LineKernel *find_copy_kernel(int M, int mode, bool uni) {
    (const void *)&k_win<1, M, MODE, 0, UNI, WIN_MOVE>, nullptr}
 static const WinKernel kWinCopy[] = {
     CB_WIN_COPY(8, MODE_X, true),  CB_WIN_COPY(10, MODE_X, true),  CB_WIN_COPY(12, MODE_X, true),
-    CB_WIN_COPY(16, MODE_X, true), CB_WIN_COPY(20, MODE_X, true),  CB_WIN_COPY(24, MODE_X, true),
+    CB_WIN_COPY(16, MODE_X, true), CB_WIN_COPY(8, MODE_X, false),  CB_WIN_COPY(12, MODE_X, false),
+    CB_WIN_COPY(16, MODE_X, false), CB_WIN_COPY(20, MODE_X, true),  CB_WIN_COPY(24, MODE_X, true),
     CB_WIN_COPY(8, MODE_S, true),  CB_WIN_COPY(12, MODE_S, true),  CB_WIN_COPY(16, MODE_S, true),
     CB_WIN_COPY(8, MODE_S, false), CB_WIN_COPY(12, MODE_S, false), CB_WIN_COPY(16, MODE_S, false),
 };

@@ -178,6 +178,18 @@ const WinKernel *win_table_r2_s(int *count);
 const WinKernel *win_table_r3_x(int *count);
 const WinKernel *win_table_r3_s(int *count);
 
+const WinKernel *win_table_rows_r1(int *count);
+const WinKernel *win_table_rows_r2(int *count);
+const WinKernel *win_table_rows_r3(int *count);
+
+const WinKernel *find_win_rows_kernel(int R, int M, int mode, int Q) {
+  int cnt = 0;
+  const WinKernel *t = R == 1 ? win_table_rows_r1(&cnt) : (R == 2 ? win_table_rows_r2(&cnt) : win_table_rows_r3(&cnt));
+  for (int i = 0; i < cnt; ++i)
+    if (t[i].M == M && t[i].mode == mode && t[i].Q == Q) return &t[i];
+  return nullptr;
+}
+
 const WinKernel *find_win_kernel(int R, int M, int mode, int Q, bool uni) {
   const WinKernel *(*const tables[])(int *) = {win_table_r1_x, win_table_r1_s, win_table_r2_x, win_table_r2_s,
                                               win_table_r3_x, win_table_r3_s};

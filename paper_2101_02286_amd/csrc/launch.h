@@ -62,6 +62,7 @@ struct WinArgs {
   int chunk_fast;            // chunks of a line are consecutive tiles
   uint32_t ltiles;           // line tiles (chunk slowest)
   int xcds;
+  int run;                   // k_win_rows: tiles per workgroup
   int nt, gcount;            // streaming loads and stores; values in g
   const double *coef, *g;
   const int *gidx;
@@ -198,6 +199,7 @@ const WgKernel *find_wg_kernel(int R, int M, int mode, int Q, bool ilu);
 // FP32 + refinement instances of the partitioned kernels (wg_fp32.hip)
 const WgKernel *find_wg32_kernel(int R, int M, int mode, int Q, bool ilu);
 const WinKernel *find_win_kernel(int R, int M, int mode, int Q, bool uni);
+const WinKernel *find_win_rows_kernel(int R, int M, int mode, int Q);
 const WinKernel *find_win_copy_kernel(int M, int mode, bool uni);
 const void *stencil_kernel(int form);
 const WinKernel *find_win_stencil_kernel(int Q);  // unit-stride lines, 16-row lanes

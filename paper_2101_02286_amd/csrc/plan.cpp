@@ -14,6 +14,7 @@
 #include <cmath>
 #include <cstring>
 #include <functional>
+#include <initializer_list>
 
 namespace cb {
 namespace {
@@ -920,13 +921,40 @@ int auto_refine_iters(const cb_plan_desc &d) {
 // a line of two sizes would read window rows of their own (tenth-order
 // derivative, n = 300 on ragged planes: 257 GDOF/s with 25 lanes of 12 rows,
 // 212 with 19 of 15 or 16).
+//
+// Bands that vary by row (k_win_rows), GDOF/s before -> after at n = 300, x / z:
+// tridiagonal 149 / 186 -> 231 / 349, pentadiagonal 86 / 139 -> 196 / 301,
+// heptadiagonal 66 / 91 -> 121 / 208.  Strided lanes without a shorter size among
+// them where 12 or 16 divides the line (n = 300 tridiagonal 349 with 25 lanes of
+// 12 rows, 297 with 19 of 15 or 16; pentadiagonal n = 192 315 with 12 rows, 262
+// with 16, 252 with 8), 8 rows where that leaves wavefronts full (n = 64 343 against
+// 286 with 16).  Unit-stride lanes that fill a wavefront's 64 (pentadiagonal
+// n = 128 8 / 16 rows 224 / 205, n = 256 16 / 12 rows 203 / 189).  Where the general
+// kernel was as fast it stays: uniform tridiagonal unit-stride lines of up to 256
+// rows (n = 128 316 against 312), others and heptadiagonal ones of up to 64 (175
+// against 148).
 static void choose_windows(const cb_plan_desc &d, Plan &p) {
-  if (d.per_row || d.rows_per_lane || d.lines_per_wg || d.block_barriers || d.x_staging || d.interior) return;
+  if (d.rows_per_lane || d.lines_per_wg || d.block_barriers || d.x_staging || d.interior) return;
   if (d.precision == CB_FP32) return;
   const int n = d.n, R = d.r;
   const bool cyclic = d.cyclic != 0;
   const int parts = d.partitions > 1 ? d.partitions : 0;
   const double tol = std::ldexp(1.0, -57);
+  if (d.per_row) {
+    auto rows = [&](std::initializer_list<int> order, WinLayout &w) {
+      for (int M : order)
+        if (M && !w.M && !build_window_rows(n, R, p.bands.data(), cyclic, M, tol, w)) w = WinLayout();
+    };
+    if (parts) return;
+    const int by12 = n % 12 == 0 ? 12 : 0, by16 = n % 16 == 0 ? 16 : 0;
+    if (R == 1 && n > 128 && (by12 || n > 256 || !p.segs[0].uniform))
+      rows({by12, n % 8 == 0 && n <= 512 ? 8 : 0, 12, 16, 8}, p.wx);
+    if (R == 2 && n > 64) rows({n % 8 == 0 && n <= 128 ? 8 : 0, n >= 256 ? by16 : 0, 12, 16, 8}, p.wx);
+    if (R == 3 && n > 64) rows({by12 && 64 % (n / 12) == 0 ? 12 : 0, 16, 12}, p.wx);
+    if (R < 3) rows({n <= 384 ? by12 : 0, n % 64 == 0 && n <= 256 ? 8 : 0, by16, 16, 12, 8}, p.ws);
+    if (R == 3 && n > 64) rows({by12, n > 128 ? 12 : 0, 16, 12}, p.ws);
+    return;
+  }
   auto build = [&](int M, bool ring, WinLayout &w) { return build_window(n, R, d.bands, cyclic, M, tol, ring, w); };
   if (cyclic && (parts || d.precision != CB_FP64 || !(p.segs[0].uniform && n <= 2048))) {
     static const int exact1[] = {12, 10, 16, 8, 20, 24}, exact2[] = {12, 16, 10, 20, 24, 8}, exact3[] = {16};

@@ -112,13 +112,15 @@ struct RedProgram {
 struct WinLayout {
   int M = 0, L = 0, base = 0, extra = 0, D = 0;  // M = 0: no such layout
   int uniform = 0;                               // cyclic, every lane M rows: one g row
-  std::vector<double> coef;                      // row[M - R][4R + 1], then z
+  int rows = 0;                                  // every lane has coefficients and a g row of its own
+  std::vector<double> coef;                      // row[M - R][4R + 1], then z (rows: per lane, win_lane_size words)
   std::vector<double> g;
   std::vector<int> gidx;
   const double *d_coef = nullptr, *d_g = nullptr;
   const int *d_gidx = nullptr;
 };
 constexpr int win_row_size(int R) { return 4 * R + 1; }
+constexpr int win_lane_size(int R, int M) { return ((M - R) * win_row_size(R) + R * R) | 1; }
 constexpr int kWinMaxD = 8;  // widest window the kernels take
 
 // Device view of a segment plan (POD, passed inside kernel arguments).
@@ -204,5 +206,8 @@ cb_status build_plan(const cb_plan_desc &d, Plan &p, std::string &msg, bool wind
 // the ceil(n / M) lanes into rows of the first); a launch computes every lane
 // from a window of lanes that are all alike.
 bool build_window(int n, int R, const double *bands, bool cyclic, int M, double tol, bool ring, WinLayout &w);
+// The same with coefficients for each lane, from the n x (2R + 1) band rows of
+// any line (entries outside an acyclic matrix zero).
+bool build_window_rows(int n, int R, const double *bands, bool cyclic, int M, double tol, WinLayout &w);
 
 }  // namespace cb

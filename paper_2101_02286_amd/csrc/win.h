@@ -146,18 +146,20 @@ __device__ __forceinline__ void win_reduce_any(const double *g, const double *gn
 // Solve the lane's rows v (b on entry, x on exit).  sh: the lane holds M - 1
 // rows.  last: the last lane of an acyclic line.  gi, gin: the lane's and the
 // next lane's row of the window table g, whose copy in LDS is gl.
-template <int R, int M, typename V, bool UNI>
+// ROW: the lane has coefficients of its own, at cf in LDS.
+template <int R, int M, typename V, bool UNI, bool ROW>
 __device__ __forceinline__ void win_solve(V (&v)[M], const double *cf, const double *g, const double *gl, int gi, int gin, const WinPos &p, V *ex,
                                           bool sh, bool last) {
   constexpr int N = M - R, RW = win_row_size(R), RR = R * R;
   const int D = p.D;
   const V zero = (V)0.0;
+  auto co = [&](int i) { return ROW ? cf[i] : cld(cf + i); };
   // z = L^{-1} b on the interior rows
 #pragma unroll
   for (int j = 1; j < N; ++j)
 #pragma unroll
     for (int q = 1; q <= R; ++q)
-      if (j - q >= 0) v[R + j] -= cld(cf + j * RW + q - 1) * v[R + j - q];
+      if (j - q >= 0) v[R + j] -= co(j * RW + q - 1) * v[R + j - q];
   if (!UNI) v[M - 1] = sh ? zero : v[M - 1];
   // c = b~ - U~ y_first, t = L~ y_last (Eq. (21))
   V ct[2 * R], xt[R], xn[R + 1], xr[R];
@@ -165,7 +167,7 @@ __device__ __forceinline__ void win_solve(V (&v)[M], const double *cf, const dou
   for (int a = 0; a < R; ++a) {
     V acc = v[a];
 #pragma unroll
-    for (int j = 0; j < N; ++j) acc -= cld(cf + j * RW + R + a) * v[R + j];
+    for (int j = 0; j < N; ++j) acc -= co(j * RW + R + a) * v[R + j];
     ct[a] = acc;
   }
   {
@@ -177,17 +179,17 @@ __device__ __forceinline__ void win_solve(V (&v)[M], const double *cf, const dou
       V acc = zero;
 #pragma unroll
       for (int i = 0; i < R; ++i) {
-        const double z0 = cld(cf + N * RW + a * R + i);
-        acc += (UNI ? z0 : (sh ? cld(cf + N * RW + RR + a * R + i) : z0)) * zl[i];
+        const double z0 = co(N * RW + a * R + i);
+        acc += (UNI || ROW ? z0 : (sh ? co(N * RW + RR + a * R + i) : z0)) * zl[i];
       }
       ct[R + a] = (!UNI && last) ? zero : acc;
     }
   }
   // x~: most wavefronts hold lanes that share one window row
-  const int gu = UNI ? 0 : __builtin_amdgcn_readfirstlane(gi);
+  const int gu = UNI || ROW ? 0 : __builtin_amdgcn_readfirstlane(gi);
   const double *gw = g + (size_t)gu * ((2 * D + 1) * RR);
   constexpr int DF = M >= 24 ? 3 : (R == 1 ? 6 : 4);  // unrolled windows
-  if (D <= DF && (UNI || __all(gi == gu && gin == gu))) {
+  if (!ROW && D <= DF && (UNI || __all(gi == gu && gin == gu))) {
     if (D == 1) win_reduce<R, 1, V>(gw, p, ex, ct, xt, xr);
     else if (D == 2) win_reduce<R, 2, V>(gw, p, ex, ct, xt, xr);
     else if (D == 3) win_reduce<R, 3, V>(gw, p, ex, ct, xt, xr);
@@ -209,11 +211,11 @@ __device__ __forceinline__ void win_solve(V (&v)[M], const double *cf, const dou
   for (int j = N - 1; j >= 0; --j) {
     V acc = v[R + j];
 #pragma unroll
-    for (int a = 0; a < R; ++a) acc -= cld(cf + j * RW + 2 * R + a) * xt[a];
-    acc *= cld(cf + j * RW + 3 * R);
+    for (int a = 0; a < R; ++a) acc -= co(j * RW + 2 * R + a) * xt[a];
+    acc *= co(j * RW + 3 * R);
 #pragma unroll
     for (int q = 1; q <= R; ++q)
-      acc -= cld(cf + j * RW + 3 * R + q) * (j + q < N ? v[j + q < N ? R + j + q : 0] : e[j + q < N ? 0 : j + q - N]);
+      acc -= co(j * RW + 3 * R + q) * (j + q < N ? v[j + q < N ? R + j + q : 0] : e[j + q < N ? 0 : j + q - N]);
     v[R + j] = (!UNI && j == N - 1) ? (sh ? xn[0] : acc) : acc;
   }
 #pragma unroll
@@ -270,16 +272,19 @@ __device__ __forceinline__ void win_store2(dbl2 v, double *q) {
 template <bool B> struct WinFlag { static constexpr bool value = B; };
 
 // What a tile's rows go through between their loads and their stores: the
-// stencil (Q > 0) and the solve, nothing, or the stencil alone.
-enum { WIN_SOLVE = 0, WIN_MOVE = 1, WIN_STENCIL = 2 };
+// stencil (Q > 0) and the solve (with one set of coefficients for all lanes, or
+// one for each), nothing, or the stencil alone.
+enum { WIN_SOLVE = 0, WIN_MOVE = 1, WIN_STENCIL = 2, WIN_ROWS = 3 };
 
 // One tile: the lanes of W lines (pairs of lines), or of one run of lanes
 // (chunk) of each of them with H halo lanes on either side.
 template <int R, int M, int MODE, int Q, bool UNI, int OP>
 __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double *smem) {
   constexpr int QQ = Q > 0 ? Q : 1;
+  constexpr bool ROW = OP == WIN_ROWS, SOLVE = OP == WIN_SOLVE || ROW;
   constexpr int KT = Q > 0 ? M + 2 : M;  // tile rows a lane loads (a window's halo needs one or two more)
-  typedef typename WinVec<win_lines(MODE)>::type VD;
+  constexpr int NL = ROW ? 2 : win_lines(MODE);  // lines per thread
+  typedef typename WinVec<NL>::type VD;
   const int tid = threadIdx.x;
   WinPos p;
   p.Lw = a.Lw;
@@ -316,7 +321,8 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
       lt = tile - ch * a.ltiles;
     }
   }
-  const int64_t line = (int64_t)lt * a.W + li;
+  constexpr int XL = MODE == MODE_X ? NL : 1;  // (strided pairs count as one line, with su = 2)
+  const int64_t line = ((int64_t)lt * a.W + li) * XL;
   const bool lactive = live && line < a.nlines;
   const FastDiv fd{a.nudiv.d, a.nudiv.mul, a.nudiv.s1, a.nudiv.s2};
   const uint32_t line32 = lactive ? (uint32_t)line : 0u;
@@ -333,7 +339,7 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
   const bool store = active && p.l >= H && p.l < H + own;
   bool sh = false;
   int m = M, start = 0;
-  if (MODE == MODE_S) {
+  if (MODE == MODE_S || !UNI) {
     if (a.acyclic) active = active && g >= 0 && g < a.L;
     g = g < 0 ? g + a.L : (g >= a.L ? g - a.L : g);
     g = g < 0 || g >= a.L ? 0 : g;  // (lanes past the last chunk's window)
@@ -346,14 +352,31 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
   const VD zero = (VD)0.0;
   // unit-stride lines go through an LDS tile: word e holds row r0 + e (modulo n)
   double *tb = nullptr;
+  auto row = [&](int w) -> VD {
+    if constexpr (XL == 2) return VD{tb[w], tb[a.pitch + w]};
+    else return (VD)tb[w];
+  };
   const double *lin = a.in + lbase;
+  int64_t other = 0;  // unit-stride pairs: from the first line to the second
+  bool two = false;
+  if (XL == 2) {
+    two = lactive && line + 1 < a.nlines;
+    const uint32_t l1 = two ? line32 + 1 : line32, v1 = fd.div(l1), u1 = l1 - v1 * a.nudiv.d;
+    other = (int64_t)u1 * a.su + (int64_t)v1 * a.sv - lbase;
+  }
   int r0 = 0, len = 0;
   // (a pad word per M words: lane l's rows are words l (M + 1) + 0..M-1, free of
   // bank conflicts; halo rows before lane 0 have negative e, words -1 - |e|)
-  auto at = [](int e) { return e + (int)((uint32_t)(e + M) / (uint32_t)M) - 1; };
+  // (lanes of two sizes: the smaller ones leave one more word unused)
+  const int big = a.extra * M;
+  auto at = [&](int e) {
+    if (UNI) return e + (int)((uint32_t)(e + M) / (uint32_t)M) - 1;
+    if (e < big || a.extra == 0) return e + (int)((uint32_t)e / (uint32_t)M);
+    return a.extra * (M + 1) + (e - big) + 2 * (int)((uint32_t)(e - big) / (uint32_t)(M - 1));
+  };
   constexpr int QP = (Q + 1) & ~1;  // halo rows beyond the window's lanes, kept even
   if constexpr (MODE == MODE_X) {
-    tb = smem + (size_t)win_planes(R, Q, MODE) * p.NS + (size_t)li * a.pitch + QP + 2;
+    tb = smem + (size_t)win_planes(R, Q, MODE) * NL * p.NS + (size_t)li * XL * a.pitch + QP + 2;
     len = a.n;
     if (a.ring) {
       r0 = ((int)ch * a.Lc - H) * M;
@@ -363,25 +386,31 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
     // pairs of rows from any 8-byte address (r0, len and QP are even); the ring
     // wraps between the rows of a pair when n is odd
     auto load = [&](auto nt) {
-      dbl2 t2[KT / 2];
+      dbl2 t2[XL][KT / 2];
 #pragma unroll
-      for (int k = 0; k < KT / 2; ++k) {
-        const int e = e0 + 2 * (p.l + k * a.Lw);
-        int r = r0 + e;
-        r = r < 0 ? r + a.n : (r >= a.n ? r - a.n : r);
-        t2[k] = dbl2{0.0, 0.0};
-        if (lactive && e < e1) {
-          if (r == a.n - 1) t2[k] = dbl2{lin[r], lin[0]};
-          else t2[k] = win_load2<decltype(nt)::value>(lin + r, false);
+      for (int h = 0; h < XL; ++h)
+#pragma unroll
+        for (int k = 0; k < KT / 2; ++k) {
+          const int e = e0 + 2 * (p.l + k * a.Lw);
+          int r = r0 + e;
+          r = r < 0 ? r + a.n : (r >= a.n ? r - a.n : r);
+          t2[h][k] = dbl2{0.0, 0.0};
+          if ((h == 0 ? lactive : two) && e < e1) {
+            const double *q = h == 0 ? lin : lin + other;
+            if (r == a.n - 1) t2[h][k] = dbl2{q[r], q[0]};  // (of a whole line the second is not kept)
+            else t2[h][k] = win_load2<decltype(nt)::value>(q + r, false);
+          }
         }
-      }
 #pragma unroll
       for (int k = 0; k < KT / 2; ++k) {
         const int e = e0 + 2 * (p.l + k * a.Lw);
         if (live && e < e1) {
-          const int w = at(e);
-          tb[w] = t2[k].x;
-          tb[w + 1] = t2[k].y;
+          const int w = at(e), w1 = UNI ? w + 1 : at(e + 1);
+#pragma unroll
+          for (int h = 0; h < XL; ++h) {
+            tb[h * a.pitch + w] = t2[h][k].x;
+            if (UNI || e + 1 < e1) tb[h * a.pitch + w1] = t2[h][k].y;
+          }
         }
       }
     };
@@ -389,7 +418,7 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
     else load(WinFlag<false>());
     p.sync();
 #pragma unroll
-    for (int k = 0; k < M; ++k) b64[k] = active ? tb[p.l * (M + 1) + k] : 0.0;
+    for (int k = 0; k < M; ++k) b64[k] = active && (UNI || k < M - 1 || !sh) ? row(p.l * (M + 1) + k) : zero;
   } else {
     const double *in = lin + (int64_t)start * a.rs;
     if (a.nt && !one) {
@@ -405,7 +434,7 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
       for (int k = 0; k < M; ++k)
         b64[k] = (active && (UNI || k < M - 1 || !sh)) ? win_load2<false>(in + k * a.rs, true) : zero;
     }
-    if (Q > 0 && OP == WIN_SOLVE) {
+    if (Q > 0 && SOLVE) {
       // the window's ends take their halo from memory
 #pragma unroll
       for (int i = 0; i < QQ; ++i) {
@@ -423,7 +452,7 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
   }
   // lanes of two sizes read different rows of the window table: copied to LDS
   // (visible after the next exchange)
-  double *gl = reinterpret_cast<double *>(smem + (size_t)win_planes(R, Q, MODE) * win_lines(MODE) * p.NS);
+  double *gl = smem + (size_t)win_planes(R, Q, MODE) * NL * p.NS + (MODE == MODE_X ? (size_t)a.W * XL * a.pitch : 0);
   if (!UNI && OP == WIN_SOLVE) {
     const double *gw = static_cast<const double *>(a.g);
     for (int i = tid; i < a.gcount; i += blockDim.x) gl[i] = gw[i];
@@ -437,8 +466,9 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
         int e = p.l * (M + 1) - 1 - Q + i, f = (p.l + 1) * (M + 1) + i;
         if (p.l == 0 && !a.ring) e = a.Lw * (M + 1) - 1 - Q + i;
         if (p.l == a.Lw - 1 && !a.ring) f = i;
-        fp[i] = active ? tb[e] : 0.0;
-        fn[i] = active ? tb[f] : 0.0;
+        if (!UNI && a.extra > 0 && (p.l == 0 || p.l > a.extra)) --e;  // the lane before holds M - 1 rows
+        fp[i] = active ? row(e) : zero;
+        fn[i] = active ? row(f) : zero;
       }
     } else {
       win_halo<QQ, M, UNI, VD>(b64, sh, p, reinterpret_cast<VD *>(smem), fp, fn);
@@ -457,28 +487,39 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
       VD acc = zero;
 #pragma unroll
       for (int q = -Q; q <= Q; ++q)  // (the stencil by itself: its own taps only, as 0 x inf is not 0)
-        if (OP == WIN_SOLVE || (q >= a.lo && q <= a.hi)) acc += a.stc[q + 3] * win_at<QQ, M, VD>(b64, fp, tail, k + q);
+        if (SOLVE || (q >= a.lo && q <= a.hi)) acc += a.stc[q + 3] * win_at<QQ, M, VD>(b64, fp, tail, k + q);
       bb[k] = (!UNI && k == M - 1 && sh) ? zero : acc;
     }
 #pragma unroll
     for (int k = 0; k < M; ++k) b64[k] = bb[k];
   }
-  if (OP == WIN_SOLVE) {
+  if (SOLVE) {
     const double *cf = static_cast<const double *>(a.coef);
     const double *gw = static_cast<const double *>(a.g);
     const int gi = UNI ? 0 : a.gidx[g], gin = UNI ? 0 : a.gidx[g + 1 < a.L ? g + 1 : 0];
     const bool last = !UNI && a.acyclic && g == a.L - 1;
     constexpr bool shared = win_shared_planes(R, Q, MODE);
-    constexpr int HP = win_halo_planes(Q, MODE) * win_lines(MODE);
+    constexpr int HP = win_halo_planes(Q, MODE) * NL;
     VD *ex = reinterpret_cast<VD *>(smem + (shared ? 0 : (size_t)HP * p.NS));
     if (shared && Q > 0) p.sync();  // the halo has been read
-    win_solve<R, M, VD, UNI>(b64, cf, gw, gl, gi, gin, p, ex, sh, last);
+    if (ROW) {  // (stride odd: no bank conflicts between a line's lanes)
+      win_solve<R, M, VD, UNI, true>(b64, gl + a.gcount + (p.live ? g : 0) * win_lane_size(R, M), gw, gl, gi, gin, p, ex, sh, last);
+    } else {
+      win_solve<R, M, VD, UNI, false>(b64, cf, gw, gl, gi, gin, p, ex, sh, last);
+    }
   }
   if constexpr (MODE == MODE_X) {
-    if (OP != WIN_SOLVE) p.sync();  // (the solve's exchange lies in between)
+    if (!SOLVE) p.sync();  // (the solve's exchange lies in between)
 #pragma unroll
     for (int k = 0; k < M; ++k)
-      if (active) tb[p.l * (M + 1) + k] = b64[k];
+      if (active && (UNI || k < M - 1 || !sh)) {
+        if constexpr (XL == 2) {
+          tb[p.l * (M + 1) + k] = b64[k].x;
+          tb[a.pitch + p.l * (M + 1) + k] = b64[k].y;
+        } else {
+          tb[p.l * (M + 1) + k] = b64[k];
+        }
+      }
     p.sync();
     double *lout = a.out + lbase;
     int s0 = 0, s1 = len;  // tile words this tile stores
@@ -492,17 +533,22 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
       for (int k = 0; k < KT / 2; ++k) {
         const int e = 2 * (p.l + k * a.Lw);
         if (lactive && e >= s0 && e < s1) {
-          double *q = lout + r0 + e;
-          const int w = at(e);
-          if (e + 1 == s1) *q = tb[w];
-          else win_store2<decltype(nt)::value>(dbl2{tb[w], tb[w + 1]}, q);
+          const int w = at(e), w1 = UNI ? w + 1 : at(e + 1);
+#pragma unroll
+          for (int h = 0; h < XL; ++h) {
+            if (h == 1 && !two) continue;
+            double *q = lout + (h == 0 ? 0 : other) + r0 + e;
+            const double *t = tb + h * a.pitch;
+            if (e + 1 == s1) *q = t[w];
+            else win_store2<decltype(nt)::value>(dbl2{t[w], t[w1]}, q);
+          }
         }
       }
     };
     if (a.nt) put(WinFlag<true>());
     else put(WinFlag<false>());
   } else {
-    if (!store) return;
+    if (!store) return;  // (no barrier follows in the tile)
     // (the output row as a distance from the input row: one address stays live)
     double *out = const_cast<double *>(lin) + (a.out - a.in) + (int64_t)start * a.rs;
     if (a.nt && !one) {
@@ -527,6 +573,11 @@ constexpr int win_max_threads() {
   return MODE == MODE_X ? 256 : 1024;
 }
 
+template <int MODE>
+constexpr int win_rows_threads() {
+  return MODE == MODE_X ? 512 : 1024;
+}
+
 template <int R, int M, int MODE, int Q, bool UNI, int OP = WIN_SOLVE>
 __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win(const WinArgs a) {
   extern __shared__ __align__(16) double smem[];
@@ -537,6 +588,36 @@ __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win(const WinA
     tile = j * q + (j < rem ? j : rem) + s;
   }
   win_tile<R, M, MODE, Q, UNI, OP>(a, tile, smem);
+}
+
+// Lanes with coefficients of their own: bands that vary by row.  The lanes'
+// coefficients and windows lie in LDS, copied once for a.run tiles, and every
+// thread takes two lines, unit-stride ones too: these are bound by LDS reads
+// (4R + 1 words a row, one line per thread 156 GDOF/s at r = 2, n = 300, two
+// 196), which the memory path of strided lines hides (301).  Unit-stride
+// workgroups fill a compute unit's LDS with two wavefronts per SIMD, so the
+// registers of four are theirs.
+template <int R, int M, int MODE, int Q>
+__global__ __launch_bounds__((win_rows_threads<MODE>()), (MODE == MODE_X ? 2 : 4)) void k_win_rows(const WinArgs a) {
+  extern __shared__ __align__(16) double smem[];
+  uint32_t blk = blockIdx.x;
+  if (a.xcds > 1) {  // grouped by XCD, as in k_line
+    const uint32_t X = (uint32_t)a.xcds, G = gridDim.x, q = G / X, rem = G % X;
+    const uint32_t j = blk % X, s = blk / X;
+    blk = j * q + (j < rem ? j : rem) + s;
+  }
+  const int NS = a.W * (a.Lw + 2 * a.D + 2);
+  double *gl = smem + (size_t)win_planes(R, Q, MODE) * 2 * NS + (MODE == MODE_X ? (size_t)a.W * 2 * a.pitch : 0);
+  for (int i = threadIdx.x; i < a.gcount; i += blockDim.x) gl[i] = a.g[i];
+  const int words = a.L * win_lane_size(R, M);
+  for (int i = threadIdx.x; i < words; i += blockDim.x) gl[a.gcount + i] = a.coef[i];
+  __syncthreads();
+  for (int i = 0; i < a.run; ++i) {
+    const uint32_t tile = blk * (uint32_t)a.run + (uint32_t)i;
+    if (tile >= a.ltiles) break;
+    if (i > 0) __syncthreads();  // (the tile before has read the planes)
+    win_tile<R, M, MODE, Q, false, WIN_ROWS>(a, tile, smem);
+  }
 }
 
 // Batched launch over the tiles of many items of one instance, as k_batched.
@@ -606,6 +687,11 @@ const void *win_batched() {
    win_batched<R, M, MODE, Q, UNI>()}
 #define CB_WIN_U(R, M, MODE, U) \
   CB_WIN_INST(R, M, MODE, 0, U), CB_WIN_INST(R, M, MODE, 2, U), CB_WIN_INST(R, M, MODE, 3, U)
+#define CB_WIN_ROWS_INST(R, M, MODE, Q)                                                       \
+  {R, M, MODE, Q, false, win_rows_threads<MODE>(), win_planes(R, Q, MODE) * 2, \
+   (const void *)&k_win_rows<R, M, MODE, Q>, nullptr}
+#define CB_WIN_ROWS(R, M, MODE) \
+  CB_WIN_ROWS_INST(R, M, MODE, 0), CB_WIN_ROWS_INST(R, M, MODE, 2), CB_WIN_ROWS_INST(R, M, MODE, 3)
 #define CB_WIN_X(R, M) CB_WIN_U(R, M, MODE_X, true)
 // the stencil by itself on unit-stride lines, in lanes of 16 rows
 #define CB_WIN_STENCIL(Q)                                                                              \

@@ -356,4 +356,172 @@ bool build_window(int n, int R, const double *bands, bool cyclic, int M, double 
   return true;
 }
 
+bool build_window_rows(int n, int R, const double *bands, bool cyclic, int M, double tol, WinLayout &w) {
+  using namespace window;
+  const int W = 2 * R + 1, RR = R * R, RW = win_row_size(R);
+  const int L = (n + M - 1) / M;
+  if (L < 2 || L > 64 || (n + L - 1) / L != M || n / L < 2 * R + 1) return false;
+  w = WinLayout();
+  const int base = n / L, extra = n % L;
+  auto a = [&](int g, int o) { return o < -R || o > R ? 0.0 : bands[(size_t)g * W + o + R]; };
+  auto start = [&](int l) { return l * base + std::min(l, extra); };
+  auto wrap = [&](int l) { return l < 0 ? l + L : (l >= L ? l - L : l); };
+  auto rows_of = [&](int l) { return base + (l < extra ? 1 : 0) - R; };  // interior
+  std::vector<Blk> Sf(L), Sl(L), Rf(L), Rl(L), Lt(L), Dt(L), Ut(L);
+  w.coef.assign((size_t)L * win_lane_size(R, M), 0.0);
+  for (int l = 0; l < L; ++l) {
+    const int i0 = start(l), m = rows_of(l), g0 = i0 + R;
+    for (int i = 0; i < R; ++i)
+      for (int c = 0; c < R; ++c) {
+        Lt[l].v[i * R + c] = a(i0 + i, c - R - i);
+        Dt[l].v[i * R + c] = a(i0 + i, c - i);
+        Ut[l].v[i * R + c] = a(i0 + i, R + c - i);
+      }
+    // elimination of the interior; columns from m on are the next lane's
+    std::vector<double> c((size_t)m * W), k((size_t)m * R, 0.0), u((size_t)m * R, 0.0), dinv(m);
+    for (int j = 0; j < m; ++j)
+      for (int o = -R; o <= R; ++o) c[(size_t)j * W + o + R] = j + o < 0 ? 0.0 : a(g0 + j, o);
+    for (int j = 0; j < m; ++j) {
+      double scale = 0.0;
+      for (int o = -R; o <= R; ++o) scale = std::max(scale, std::fabs(a(g0 + j, o)));
+      const double piv = c[(size_t)j * W + R];
+      if (!(std::fabs(piv) > 1e-2 * scale) || !std::isfinite(piv)) return false;
+      dinv[j] = 1.0 / piv;
+      for (int i = j + 1; i <= std::min(m - 1, j + R); ++i) {
+        const double f = c[(size_t)i * W + (j - i + R)] / piv;
+        k[(size_t)i * R + (i - j) - 1] = f;
+        for (int q = j + 1; q <= j + R; ++q) c[(size_t)i * W + (q - i + R)] -= f * c[(size_t)j * W + (q - j + R)];
+      }
+      for (int q = 1; q <= R; ++q) u[(size_t)j * R + q - 1] = c[(size_t)j * W + R + q] * dinv[j];
+    }
+    auto forward = [&](double *x) {
+      for (int j = 1; j < m; ++j)
+        for (int q = 1; q <= R && q <= j; ++q) x[j] -= k[(size_t)j * R + q - 1] * x[j - q];
+    };
+    auto backward = [&](double *x) {
+      for (int j = m - 1; j >= 0; --j) {
+        double s = x[j] * dinv[j];
+        for (int q = 1; q <= R && j + q < m; ++q) s -= u[(size_t)j * R + q - 1] * x[j + q];
+        x[j] = s;
+      }
+    };
+    double *row = w.coef.data() + (size_t)l * win_lane_size(R, M);
+    std::vector<double> wf((size_t)R * m, 0.0), x(m);  // first R rows of U^{-1}
+    for (int i = 0; i < R; ++i) {
+      std::vector<double> p(m + R, 0.0);
+      p[i] = 1.0;
+      for (int j = i; j < m; ++j) {
+        wf[(size_t)i * m + j] = p[j] * dinv[j];
+        for (int q = 1; q <= R; ++q) p[j + q] -= p[j] * u[(size_t)j * R + q - 1];
+      }
+    }
+    for (int s = 0; s < R; ++s) {
+      for (int j = 0; j < m; ++j) x[j] = a(g0 + j, s - R - j);
+      forward(x.data());
+      for (int j = 0; j < m; ++j) row[(size_t)j * RW + 2 * R + s] = x[j];
+      backward(x.data());
+      for (int i = 0; i < R; ++i) {
+        Sf[l].v[i * R + s] = x[i];
+        Sl[l].v[i * R + s] = x[m - R + i];
+      }
+      for (int j = 0; j < m; ++j) x[j] = a(g0 + j, m + s - j);
+      forward(x.data());
+      backward(x.data());
+      for (int i = 0; i < R; ++i) {
+        Rf[l].v[i * R + s] = x[i];
+        Rl[l].v[i * R + s] = x[m - R + i];
+      }
+    }
+    double biggest = 0.0, top = 1.0;
+    for (int j = 0; j < m; ++j) {
+      double *t = row + (size_t)j * RW;
+      for (int q = 0; q < R; ++q) {
+        t[q] = k[(size_t)j * R + q];
+        t[3 * R + 1 + q] = u[(size_t)j * R + q];
+        for (int i = 0; i < R; ++i) t[R + q] += Ut[l].v[q * R + i] * wf[(size_t)i * m + j];
+      }
+      t[3 * R] = dinv[j];
+      for (int q = 0; q < RW; ++q)
+        if (q != 3 * R) biggest = std::max(biggest, std::fabs(t[q]));
+      for (int o = -R; o <= R; ++o) top = std::max(top, std::fabs(a(g0 + j, o)));
+    }
+    if (!(biggest <= 64.0 * top)) return false;  // elimination that grows needs pivoting
+    // z: the next lane's L~ times the last R rows of U^{-1}, on the last R values of z
+    const int nx = wrap(l + 1), ni = start(nx);
+    for (int i = 0; i < R; ++i) {
+      std::fill(x.begin(), x.end(), 0.0);
+      x[m - R + i] = 1.0;
+      backward(x.data());
+      for (int b = 0; b < R; ++b)
+        for (int s = 0; s < R; ++s) row[(size_t)(M - R) * RW + b * R + i] += a(ni + b, s - R - b) * x[m - R + s];
+    }
+  }
+  // the reduced system (Eqs. (18)-(20)) and its dense inverse
+  const int m = L * R;
+  std::vector<double> t((size_t)m * m, 0.0), inv((size_t)m * m);
+  double scale = 0.0;
+  for (int l = 0; l < L; ++l) {
+    const int lm = wrap(l - 1), lp = wrap(l + 1);
+    const bool first = !cyclic && l == 0, last = !cyclic && l == L - 1;
+    Blk di = sub(Dt[l], mul(Ut[l], Sf[l], R), R), lo, up;
+    if (!first) {
+      di = sub(di, mul(Lt[l], Rl[lm], R), R);
+      lo = neg(mul(Lt[l], Sl[lm], R), R);
+    }
+    if (!last) up = neg(mul(Ut[l], Rf[l], R), R);
+    for (int i = 0; i < R; ++i)
+      for (int c = 0; c < R; ++c) {
+        t[(size_t)(l * R + i) * m + lm * R + c] += lo.v[i * R + c];
+        t[(size_t)(l * R + i) * m + l * R + c] += di.v[i * R + c];
+        t[(size_t)(l * R + i) * m + lp * R + c] += up.v[i * R + c];
+      }
+  }
+  for (int i = 0; i < n * W; ++i) scale = std::max(scale, std::fabs(bands[i]));
+  if (!invert(m, t.data(), inv.data())) return false;
+  // the narrowest window that leaves out no more than tol of any lane's row
+  auto dist = [&](int l, int j) {
+    int d = j - l;
+    if (cyclic && d > L / 2) d -= L;
+    if (cyclic && d < -((L - 1) / 2)) d += L;
+    return d;
+  };
+  int D = 1;
+  for (int l = 0; l < L; ++l) {
+    std::vector<double> far(L + 1, 0.0);
+    double sum = 0.0;
+    for (int j = 0; j < L; ++j)
+      for (int i = 0; i < R; ++i)
+        for (int c = 0; c < R; ++c) {
+          const double v = std::fabs(inv[(size_t)(l * R + i) * m + j * R + c]);
+          far[std::abs(dist(l, j))] += v;
+          sum += v;
+        }
+    if (!std::isfinite(sum) || !(sum * scale <= 1e4)) return false;
+    double out = 0.0;
+    int d = L;
+    while (d > 0 && out + far[d] <= tol * sum) out += far[d--];
+    D = std::max(D, d);
+  }
+  if (D > kWinMaxD || D > L - 1) return false;
+  w.M = M;
+  w.L = L;
+  w.base = base;
+  w.extra = extra;
+  w.D = D;
+  w.rows = 1;
+  w.gidx.resize(L);
+  w.g.assign((size_t)L * (2 * D + 1) * RR, 0.0);
+  for (int l = 0; l < L; ++l) {
+    w.gidx[l] = l;
+    for (int j = 0; j < L; ++j) {
+      const int d = dist(l, j);
+      if (std::abs(d) > D) continue;
+      for (int i = 0; i < R; ++i)
+        for (int c = 0; c < R; ++c)
+          w.g[((size_t)l * (2 * D + 1) + D + d) * RR + i * R + c] = inv[(size_t)(l * R + i) * m + j * R + c];
+    }
+  }
+  return true;
+}
+
 }  // namespace cb

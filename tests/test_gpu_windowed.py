@@ -99,3 +99,25 @@ def test_refined_plans(gpu, axis, band, n):
         plan = cb.Plan(BANDS[band], n, precision="fp32_refine", refine_iters=iters)
         x = cb.apply_derivative(plan, cb.Stencil(lo, c), f.to(gpu), axis).cpu().numpy()
         assert relerr(x, ref) <= TOL
+
+
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("r", [1, 2, 3])
+@pytest.mark.parametrize("cyclic", [True, False])
+@pytest.mark.parametrize("n", [24, 41, 64, 100, 129, 250, 300, 512, 613, 701, 1000])
+def test_bands_by_row(gpu, axis, r, cyclic, n):
+    """Lanes with coefficients of their own, odd numbers of lines, in place."""
+    shape = grid(axis, n, (35, 3))
+    bands = synth.random_bands(n, r, seed=n)
+    b = synth.random_uniform(shape, seed=n + r)
+    ref = oracle.solve_axis(b.numpy(), axis, bands, cyclic=cyclic, per_row=True)
+    plan = cb.Plan(bands, n, cyclic=cyclic, per_row=True)
+    x = b.to(gpu)
+    assert relerr(cb.solve(plan, x, axis).cpu().numpy(), ref) <= TOL
+    cb.solve(plan, x, axis, out=x)
+    assert relerr(x.cpu().numpy(), ref) <= TOL
+    if cyclic:
+        lo, c = STENCILS["tri" if r == 1 else "penta"]
+        x = cb.apply_derivative(plan, cb.Stencil(lo, c), b.to(gpu), axis).cpu().numpy()
+        rhs = sum(ck * np.roll(b.numpy(), -(lo + k), 2 - axis) for k, ck in enumerate(c))
+        assert relerr(x, oracle.solve_axis(rhs, axis, bands, per_row=True)) <= TOL

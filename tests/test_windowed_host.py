@@ -2,7 +2,8 @@
 host under AddressSanitizer (tests/windowed_host.cpp) and compared with the
 oracle: lines that split into lanes of one size or of two, rings around a line
 that no row count divides, lines in several chunks, odd and even numbers of
-lines, padded rows, in-place calls, acyclic lines, partitions and batches."""
+lines, padded rows, in-place calls, acyclic lines, bands that vary by row, partitions
+and batches."""
 import os
 import subprocess
 
@@ -43,6 +44,17 @@ WINDOWED = """
 1 384 0 3 2 1 1 0 2 1 0 0
 2 128 0 5 1 0 1 3 2 0 0 1
 1 200 2 9 2 0 1 0 2 1 0 0
+1 144 0 30 3 0 2 0 0 0 0 0
+1 301 0 4 2 1 3 2 0 0 0 0
+1 1000 0 3 1 1 3 3 0 0 0 0
+2 72 0 23 1 0 3 3 0 0 0 0
+2 300 0 5 3 1 2 0 0 1 0 0
+2 256 0 5 1 0 3 2 2 0 0 0
+3 139 0 4 2 0 2 0 0 0 0 0
+1 130 1 5 3 1 2 0 0 0 0 0
+2 40 2 3 7 0 3 3 0 0 0 0
+2 256 1 33 2 0 2 0 0 1 0 0
+3 300 2 5 2 0 3 2 0 0 0 0
 0 32 0 5 3 0 1 2 0 0 0 0
 0 33 0 7 2 1 1 3 0 0 0 0
 0 48 0 3 3 0 1 2 0 0 0 0
@@ -50,11 +62,13 @@ WINDOWED = """
 0 1025 0 3 2 1 1 1 0 0 0 0
 0 2071 0 2 2 0 1 3 0 0 0 0
 """
-# in place in several chunks, unit-stride acyclic lines, plain FP32: the general kernels
+# in place in several chunks, unit-stride acyclic lines, short ones with
+# tridiagonal bands that vary by row, plain FP32: the general kernels
 GENERAL = """
 1 1700 1 4 2 0 1 0 0 1 0 0
 1 1900 0 2 2 0 1 0 0 1 0 0
 1 300 0 2 2 0 0 0 0 0 0 0
+1 100 0 2 2 0 2 0 0 0 0 0
 1 300 1 4 2 0 1 2 1 0 0 0
 """
 

@@ -2,7 +2,7 @@
 // per work item, AddressSanitizer over exact-size buffers and LDS), through the
 // C ABI, against the oracle.  Reads one case per line:
 //   r n axis d0 d1 pitch cyclic halfwidth precision in_place partitions batch
-// (d0, d1: the other extents in axis order; pitch: spare elements per x row;
+// (cyclic: + 2 for bands that vary by row; d0, d1: the other extents in axis order; pitch: spare elements per x row;
 // halfwidth 0: plain solve; r = 0: the stencil by itself) and prints "ok" or "BAD", whether a windowed kernel
 // ran, and the relative error.
 #include <hip/hip_runtime.h>
@@ -34,6 +34,15 @@ static const WinKernel kTable[] = {
 const WinKernel *find_win_kernel(int R, int M, int mode, int Q, bool uni) {
   for (const auto &k : kTable)
     if (k.R == R && k.M == M && k.mode == mode && k.Q == Q && k.uni == uni) return &k;
+  return nullptr;
+}
+const WinKernel *find_win_rows_kernel(int R, int M, int mode, int Q) {
+  static const WinKernel t[] = {CB_WIN_ROWS(1, 8, MODE_X),  CB_WIN_ROWS(1, 12, MODE_X), CB_WIN_ROWS(1, 16, MODE_X),
+                                CB_WIN_ROWS(2, 8, MODE_X),  CB_WIN_ROWS(2, 12, MODE_X), CB_WIN_ROWS(2, 16, MODE_X), CB_WIN_ROWS(3, 16, MODE_X),
+                                CB_WIN_ROWS(1, 12, MODE_S), CB_WIN_ROWS(1, 16, MODE_S), CB_WIN_ROWS(2, 8, MODE_S),
+                                CB_WIN_ROWS(2, 16, MODE_S), CB_WIN_ROWS(3, 12, MODE_S)};
+  for (const auto &k : t)
+    if (k.R == R && k.M == M && k.mode == mode && k.Q == Q) return &k;
   return nullptr;
 }
 // anything else is named but not run
@@ -103,7 +112,18 @@ int main() {
     cb_plan_desc d = {};
     d.r = r;
     d.n = n;
-    d.bands = kBands[r].data();
+    const bool rows = cyclic >= 2;
+    cyclic &= 1;
+    std::vector<double> bands = kBands[r];
+    if (rows) {
+      std::mt19937_64 gen(7 * n + r);
+      std::uniform_real_distribution<double> u(0.5, 1.5);
+      bands.clear();
+      for (int j = 0; j < n; ++j)
+        for (double v : kBands[r]) bands.push_back(v * u(gen) * (v == 1 ? 2 : 1));
+    }
+    d.bands = bands.data();
+    d.per_row = rows;
     d.cyclic = cyclic;
     d.precision = prec;
     d.partitions = parts;
@@ -151,7 +171,7 @@ int main() {
             rhs[j] += st.coef[q + half] * b0[base + ((j + q + n) % n) * g.stride[axis]];
         }
         x = rhs;
-        if (r) orc_solve_lines(r, n, kBands[r].data(), 0, cyclic, 1, rhs.data(), x.data());
+        if (r) orc_solve_lines(r, n, bands.data(), rows, cyclic, 1, rhs.data(), x.data());
         for (int j = 0; j < n; ++j) {
           const int64_t at = base + j * g.stride[axis];
           inside[at] = 1;
@@ -161,8 +181,8 @@ int main() {
       }
     bool ok = s == CB_OK && (!ran || err <= (prec == CB_FP32 ? 3e-6 : 1e-12) * top);
     for (size_t i = 0; i < span; ++i) ok = ok && (inside[i] || out[i] == (in_place ? b0[i] : 7.0));  // no stray stores
-    printf("%s windowed=%d err=%.2g: r%d n%d axis%d %dx%d+%d cyclic%d half%d prec%d in_place%d parts%d batch%d\n",
-           ok ? "ok" : "BAD", ran, err / top, r, n, axis, d0, d1, pitch, cyclic, half, prec, in_place, parts, batch);
+    printf("%s windowed=%d err=%.2g: r%d n%d axis%d %dx%d+%d rows%d cyclic%d half%d prec%d in_place%d parts%d batch%d\n",
+           ok ? "ok" : "BAD", ran, err / top, r, n, axis, d0, d1, pitch, rows, cyclic, half, prec, in_place, parts, batch);
     fflush(stdout);
     bad += !ok;
     if (r) cb_plan_destroy(p);
