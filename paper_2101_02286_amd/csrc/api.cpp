@@ -439,10 +439,28 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
       if (!split(64) || a.n < (halo + 1) * wl.M + 4) return false;
     }
     int waves = p.R == 1 ? 4 : 1;  // (wider bands: one measured 2-10 % faster, tridiagonal ones four)
-    if (wl.rows) waves = p.R == 1 && a.Lw > 32 && !small ? 8 : 4;
     w.threads = 64 * waves;
     a.lpw = 64 / a.Lw;
     a.linv = (65536 + a.Lw - 1) / a.Lw;
+    if (wl.rows && how != WIN_COPY) {
+      // the workgroup size that brings most wavefronts (up to two per SIMD) onto a
+      // compute unit beside their coefficient tables (n = 300 pentadiagonal with
+      // window half-width 3: 115 GDOF/s with 4, 180 with 8; n = 701 tridiagonal
+      // 185 with 4, 254 with 8); the general kernel below four (n = 1000
+      // heptadiagonal 77 against 29)
+      const size_t table = wl.g.size() + wl.coef.size();
+      const size_t wave = (size_t)a.lpw * ((size_t)w.k->lds * (a.Lw + 2 * a.D + 2) + 2 * ((a.Lw * (wl.M + 1) + 2 * QP + 4) & ~1));
+      int most = 0;
+      for (int v : {4, 8, 7, 6, 5, 3, 2, 1}) {
+        const int on = std::min<int>(8, v * (int)(lds_cap() / ((table + v * wave) * sizeof(double))));
+        if (on > most) {
+          most = on;
+          waves = v;
+        }
+      }
+      if (most < 4) return false;
+      w.threads = 64 * waves;
+    }
     a.W = waves * a.lpw;
     a.pitch = (a.Lw * (wl.M + 1) + 2 * QP + 4) & ~1;
     a.nt = a.H == 0 ? 1 : 0;
@@ -492,7 +510,7 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
     // several tiles per workgroup where the copy of the lanes' coefficients
     // weighs: unit-stride lines of many lanes or r = 3 (n = 701 pentadiagonal
     // 117 -> 140, 512 181 -> 197 GDOF/s; 300 196 -> 176; strided 301 -> 291)
-    const bool several = mode == MODE_X && (p.R == 3 || (a.Lw >= 32 && w.threads == 256));
+    const bool several = mode == MODE_X && (p.R == 3 || a.Lw >= 32);
     a.run = several ? (int)std::min<int64_t>(3, std::max<int64_t>(1, ltiles / 1024)) : 1;
     w.blocks = (ltiles + a.run - 1) / a.run;
   }
