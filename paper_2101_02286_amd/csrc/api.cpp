@@ -30,10 +30,12 @@ struct BatchLaunch {
   size_t hdr_off, items_off, lds;
   int threads;
   int64_t tiles;
+  int item;  // of one item only: its index in BatchState::own, else -1
 };
 // An item with launches of its own: lines split over P > 1 workgroup
 // partitions (its phase launches, with its partition scratch in the workspace),
-// or lanes with coefficients of their own (cb_solve's launch).
+// or lanes with coefficients of their own (cb_solve's launch).  Also the items
+// that have a class to themselves, for launches with a workgroup per tile.
 struct OwnItem {
   cb_plan_t plan;
   const Plan *wp;  // partitioned: the plan (P > 1) or its partitioned strided copy; else null
@@ -44,6 +46,7 @@ struct OwnItem {
   bool has_stencil;
   cb_stencil stencil;
   size_t sc_off, sc_bytes;
+  bool always;  // not in the work table
 };
 // Per workspace: its launches, the pinned host copy its table is uploaded
 // from, and the event recorded on the build stream after that upload.
@@ -1112,13 +1115,13 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
   if (!workspace || workspace_bytes < need)
     return fail(CB_ERR_INVALID_ARG, "cb_batch_build: workspace missing or too small (needs " + std::to_string(need) +
                                         " bytes: cb_batch_workspace_bytes)");
-  std::vector<OwnItem> own;
+  std::vector<OwnItem> own, each;
   size_t sc_next = align256(batch_items_offset((size_t)n_items) + (size_t)n_items * sizeof(BatchItemDev));
   struct Cls {
     const void *fn;
     int threads;
     size_t lds;
-    bool win;
+    bool win, alone;
     std::vector<int> members;
   };
   std::vector<Cls> cls;
@@ -1140,6 +1143,25 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
       if (!p.desc.cyclic) return fail(CB_ERR_INVALID_ARG, "cb_batch_build: a stencil needs a cyclic plan");
     }
     if (g.nlines >= (int64_t(1) << 31)) return fail(CB_ERR_UNSUPPORTED, "cb_batch_build: more than 2^31 lines");
+    // A large item has a launch of its own: its arguments then come with the
+    // launch, where a workgroup of a shared one searches the table and reads
+    // them from memory (384^3 sixth-order along x 152 -> 143 us).
+    // From 2^24 points (~50 us) on the time between launches does not show.
+    // FP32 strided lines run faster from the table (384^3 215-226 GDOF/s
+    // against 173).
+    const bool alone = g.nlines * g.n >= (int64_t(1) << 24) && p.precision != CB_FP32;
+    OwnItem own_item;
+    own_item.plan = it.plan;
+    own_item.wp = nullptr;
+    own_item.grid = it.grid;
+    own_item.axis = it.axis;
+    own_item.in = it.in;
+    own_item.out = it.out;
+    own_item.has_stencil = it.stencil != nullptr;
+    if (it.stencil) own_item.stencil = *it.stencil;
+    own_item.sc_off = own_item.sc_bytes = 0;
+    own_item.always = false;
+    each.push_back(own_item);
     WinLaunch w;
     if (win_config(p, g, it.in, it.out, it.stencil, WIN_BATCH, w)) {
       WinItemDev d;
@@ -1151,8 +1173,8 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
       // items of one instance share a launch: unit-stride ones have one
       // workgroup size, strided ones take the largest of theirs
       int c = 0;
-      while (c < (int)cls.size() && cls[c].fn != w.k->batch_fn) ++c;
-      if (c == (int)cls.size()) cls.push_back(Cls{w.k->batch_fn, 0, 0, true, {}});
+      while (c < (int)cls.size() && (alone || cls[c].alone || cls[c].fn != w.k->batch_fn)) ++c;
+      if (c == (int)cls.size()) cls.push_back(Cls{w.k->batch_fn, 0, 0, true, alone, {}});
       cls[c].threads = std::max(cls[c].threads, w.threads);
       cls[c].lds = std::max(cls[c].lds, w.lds);
       cls[c].members.push_back(i);
@@ -1162,15 +1184,9 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
                       (g.rs == 1 ? p.wx : p.ws).rows;
     const Plan *wp = rows ? nullptr : batch_wg_plan(p, g);
     if (rows || wp) {  // its own launches, scratch in the workspace
-      OwnItem w;
-      w.plan = it.plan;
+      OwnItem w = each.back();
       w.wp = wp;
-      w.grid = it.grid;
-      w.axis = it.axis;
-      w.in = it.in;
-      w.out = it.out;
-      w.has_stencil = it.stencil != nullptr;
-      if (it.stencil) w.stencil = *it.stencil;
+      w.always = true;
       w.sc_bytes = wp ? wg_scratch_bytes(*wp, g.nlines) : 0;
       w.sc_off = sc_next;
       sc_next += align256(w.sc_bytes);
@@ -1277,8 +1293,8 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
     d.mode = mode;
     ntiles[i] = (g.nlines + W - 1) / W;
     int c = 0;
-    while (c < (int)cls.size() && !(cls[c].fn == fn && cls[c].threads == nt)) ++c;
-    if (c == (int)cls.size()) cls.push_back(Cls{fn, nt, 0, false, {}});
+    while (c < (int)cls.size() && (alone || cls[c].alone || !(cls[c].fn == fn && cls[c].threads == nt))) ++c;
+    if (c == (int)cls.size()) cls.push_back(Cls{fn, nt, 0, false, alone, {}});
     cls[c].lds = std::max(cls[c].lds, lds);
     cls[c].members.push_back(i);
   }
@@ -1315,9 +1331,12 @@ cb_status cb_batch_build(const cb_batch_item *items, int32_t n_items, void *work
     h.n_items = (int)cls[c].members.size();
     h.total_tiles = tiles;
     std::memcpy(host.data() + c * kBatchHdrBytes, &h, sizeof(h));
+    // (four served requests, each of an instance of its own: 239 -> 221 us)
+    const bool single = cls[c].members.size() == 1 && items[cls[c].members[0]].plan->p.precision != CB_FP32;
     launches.push_back({cls[c].fn, c * kBatchHdrBytes,
                         batch_items_offset(n_items) + (slot - cls[c].members.size()) * sizeof(BatchItemDev),
-                        cls[c].lds, cls[c].threads, tiles});
+                        cls[c].lds, cls[c].threads, tiles, single ? (int)own.size() : -1});
+    if (single) own.push_back(each[cls[c].members[0]]);
   }
   // The table goes up from a pinned buffer kept per workspace, in stream
   // order, without waiting on the host: a serving loop keeps admitting work
@@ -1410,7 +1429,20 @@ cb_status cb_batch_launch(void *workspace, int32_t max_ctas, void *stream) {
   e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return hip_fail(e, "cb_batch_launch: device query");
+  auto launch_own = [&](const OwnItem &w) -> cb_status {
+    Geo g;
+    const cb_status s = geometry(&w.grid, w.axis, g);
+    if (s || g.nlines == 0) return s;
+    const FixedScratch fs{static_cast<char *>(workspace) + w.sc_off, w.sc_bytes};
+    const cb_stencil *st = w.has_stencil ? &w.stencil : nullptr;
+    return w.wp ? launch_wg(*w.wp, g, w.in, w.out, st, ls_stream, &fs) : launch(w.plan->p, g, w.in, w.out, st, ls_stream, nullptr);
+  };
   for (const BatchLaunch &l : ls) {
+    if (max_ctas < 0 && l.item >= 0) {
+      const cb_status s = launch_own(own[l.item]);
+      if (s) return s;
+      continue;
+    }
     int per_cu = 0;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, l.fn, l.threads, l.lds);
     if (e != hipSuccess) return hip_fail(e, "cb_batch_launch: occupancy query");
@@ -1431,13 +1463,7 @@ cb_status cb_batch_launch(void *workspace, int32_t max_ctas, void *stream) {
   // items with launches of their own (partition scratch in the workspace: no
   // allocation, so capturable)
   for (const OwnItem &w : own) {
-    Geo g;
-    cb_status s = geometry(&w.grid, w.axis, g);
-    if (s) return s;
-    if (g.nlines == 0) continue;
-    const FixedScratch fs{static_cast<char *>(workspace) + w.sc_off, w.sc_bytes};
-    const cb_stencil *st = w.has_stencil ? &w.stencil : nullptr;
-    s = w.wp ? launch_wg(*w.wp, g, w.in, w.out, st, ls_stream, &fs) : launch(w.plan->p, g, w.in, w.out, st, ls_stream, nullptr);
+    const cb_status s = w.always ? launch_own(w) : CB_OK;
     if (s) return s;
   }
   return CB_OK;
