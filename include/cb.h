@@ -227,7 +227,9 @@ typedef struct {
 /* Batched execution: the lines of many items -- uneven grids, any axes,
  * different plans -- run in ONE kernel launch per kernel class present in the
  * batch, either persistent (a resident grid takes line tiles from a device
- * work queue) or with one workgroup per line tile
+ * work queue) or with one workgroup per line tile (large items, and items alone
+ * in their class, then take the launch of a single call; items with bands that
+ * vary by row always do)
  * (a class is r, rows per lane, arithmetic, uniform or general lane layout,
  * interior solve, unit-stride or strided rows and stencil half-width (2 or
  * 3), as an item's plan, row stride and stencil select them; a batch of plans built alike for one scheme and
@@ -271,7 +273,10 @@ cb_status cb_solve_batched(const cb_batch_item *items, int32_t n_items, void *wo
 typedef struct {
   int32_t r, n, cyclic, precision, refine_iters;
   int32_t partitions;      /* P workgroup partitions */
-  int32_t lanes;           /* L lanes (sub-partitions) per segment */
+  int32_t lanes;           /* L lanes (sub-partitions) per segment; this and the
+                              layouts below describe the general kernels:
+                              windowed lanes, which automatic plans run where
+                              they apply, have layouts of their own */
   int32_t rows_per_lane;   /* M register slots per lane */
   int32_t uniform;         /* 1: every lane partition identical */
   int32_t interior_levels; /* generalized-PCR levels inside a lane partition */
