@@ -517,6 +517,16 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
     a.run = several ? (int)std::min<int64_t>(3, std::max<int64_t>(1, ltiles / 1024)) : 1;
     w.blocks = (ltiles + a.run - 1) / a.run;
   }
+  // Chunks of whole cache lines in fields that the 256 MB memory-side cache does
+  // not hold (input and output): launch order, and where rows lie 32 KB or more
+  // apart the same chunk of neighbouring lines first, so that the workgroups in
+  // flight read long runs of each row (n = 8192, 64 x 64 lines, z 208 -> 301
+  // GDOF/s, P = 16 or not; n = 2048 on 256 x 64 y 296 -> 317, z 248 -> 303; smaller
+  // fields run best grouped, n = 4096 on 64 x 64 y 392 against 364)
+  if (mode == MODE_S && a.nch > 1 && whole && p.desc.tile_order == 0 && (double)g.n * g.nlines * 8 > 160e6) {
+    a.xcds = 1;
+    a.chunk_fast = g.rs >= 4096 ? 0 : 1;
+  }
   a.coef = wl.d_coef;
   a.g = wl.d_g;
   a.gidx = wl.d_gidx;
