@@ -202,7 +202,8 @@ def headline(args):
                               for k, c, v in zip("xyz", copy_ms, per_dir_ms)},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic(dom),
-                     "kernel": "k_line %s (%s)" % (dom, ", ".join("xyz"[ax] for ax in groups[dom])),
+                     "kernel": "%s %s (%s)" % ("k_win" if "strided" in dom and not tuned else "k_line", dom,
+                                            ", ".join("xyz"[ax] for ax in groups[dom])),
                      "avg_launch_ms": round(dom_ms, 4), "bytes_per_launch": BYTES_PER_DOF * dof,
                      "copy_same_pattern_gbs": round(BYTES_PER_DOF * dof / (dom_copy_ms * 1e-3) / 1e9, 1),
                      "frac_of_copy_same_pattern": round(dom_copy_ms / dom_ms, 4)},

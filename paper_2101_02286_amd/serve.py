@@ -176,10 +176,10 @@ class GpuExecutor:
     """Runs request groups as one batched launch per stream slot.
 
     `precision` defaults to FP64: each line is read and written once either
-    way, and FP32 with FP64 refinement runs the reduction at least twice per
-    line with both precisions' state in registers, which costs more than
-    FP64 arithmetic saves (measured at saturation on the served request
-    mix: 170-173 GDOF/s FP64, 89-93 FP32 + refinement); "fp32_refine"
+    way, and FP32 with FP64 refinement either solves in FP64 too (windowed
+    lanes) or runs the reduction at least twice per line (measured at
+    saturation on the served request mix: 254 GDOF/s FP64, 260 FP32 +
+    refinement, both on windowed lanes); "fp32_refine"
     remains available."""
 
     # share of the device's free memory that admission may hand to requests
