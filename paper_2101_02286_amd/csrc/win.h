@@ -277,9 +277,10 @@ template <bool B> struct WinFlag { static constexpr bool value = B; };
 enum { WIN_SOLVE = 0, WIN_MOVE = 1, WIN_STENCIL = 2, WIN_ROWS = 3 };
 
 // One tile: the lanes of W lines (pairs of lines), or of one run of lanes
-// (chunk) of each of them with H halo lanes on either side.
+// (chunk) of each of them with H halo lanes on either side.  threads: those of
+// the workgroup that run the tile (a batched launch may have more).
 template <int R, int M, int MODE, int Q, bool UNI, int OP>
-__device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double *smem) {
+__device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double *smem, int threads) {
   constexpr int QQ = Q > 0 ? Q : 1;
   constexpr bool ROW = OP == WIN_ROWS, SOLVE = OP == WIN_SOLVE || ROW;
   constexpr int KT = Q > 0 ? M + 2 : M;  // tile rows a lane loads (a window's halo needs one or two more)
@@ -455,7 +456,7 @@ __device__ __forceinline__ void win_tile(const WinArgs &a, uint32_t tile, double
   double *gl = smem + (size_t)win_planes(R, Q, MODE) * NL * p.NS + (MODE == MODE_X ? (size_t)a.W * XL * a.pitch : 0);
   if (!UNI && OP == WIN_SOLVE) {
     const double *gw = static_cast<const double *>(a.g);
-    for (int i = tid; i < a.gcount; i += blockDim.x) gl[i] = gw[i];
+    for (int i = tid; i < a.gcount; i += threads) gl[i] = gw[i];
   }
   if (Q > 0 && OP != WIN_MOVE) {  // fused right-hand-side stencil (Eqs. (1)-(2)), periodic
     VD fp[QQ], fn[QQ], tail[QQ + 1];
@@ -587,7 +588,7 @@ __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win(const WinA
     const uint32_t j = tile % X, s = tile / X;
     tile = j * q + (j < rem ? j : rem) + s;
   }
-  win_tile<R, M, MODE, Q, UNI, OP>(a, tile, smem);
+  win_tile<R, M, MODE, Q, UNI, OP>(a, tile, smem, (int)blockDim.x);
 }
 
 // Lanes with coefficients of their own: bands that vary by row.  The lanes'
@@ -616,7 +617,7 @@ __global__ __launch_bounds__((win_rows_threads<MODE>()), (MODE == MODE_X ? 2 : 4
     const uint32_t tile = blk * (uint32_t)a.run + (uint32_t)i;
     if (tile >= a.ltiles) break;
     if (i > 0) __syncthreads();  // (the tile before has read the planes)
-    win_tile<R, M, MODE, Q, false, WIN_ROWS>(a, tile, smem);
+    win_tile<R, M, MODE, Q, false, WIN_ROWS>(a, tile, smem, (int)blockDim.x);
   }
 }
 
@@ -650,7 +651,7 @@ __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win_batched(Ba
       const uint32_t X = (uint32_t)it.a.xcds, q = G / X, rem = G % X, j = local % X, s = local / X;
       local = j * q + (j < rem ? j : rem) + s;
     }
-    win_tile<R, M, MODE, Q, UNI, WIN_SOLVE>(it.a, local, smem);
+    win_tile<R, M, MODE, Q, UNI, WIN_SOLVE>(it.a, local, smem, it.threads);
     return;
   }
   for (;;) {
@@ -661,7 +662,7 @@ __global__ __launch_bounds__((win_max_threads<MODE>()), 4) void k_win_batched(Ba
     __syncthreads();
     if (t >= total) break;
     const WinItemDev &it = items[item_of(t)];
-    win_tile<R, M, MODE, Q, UNI, WIN_SOLVE>(it.a, (uint32_t)(t - it.tile_begin), smem);
+    win_tile<R, M, MODE, Q, UNI, WIN_SOLVE>(it.a, (uint32_t)(t - it.tile_begin), smem, (int)blockDim.x);
     __syncthreads();
   }
   if (threadIdx.x == 0) {

@@ -1,0 +1,56 @@
+"""What the windowed-lane kernels read of LDS, on the host with LDS that holds NaN
+until it is written (tests/windowed_lds_host.cpp): batches whose items have
+workgroups of different sizes, in both forms."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CLANG = "/opt/rocm/llvm/bin/clang++"
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    if not os.path.exists(CLANG):
+        pytest.skip("no clang++ in the ROCm installation")
+    d = str(tmp_path_factory.mktemp("windowed_lds"))
+    src = [os.path.join(ROOT, "tests", "windowed_lds_host.cpp")] + \
+        [os.path.join(ROOT, "paper_2101_02286_amd", "csrc", f) for f in ("api.cpp", "plan.cpp")]
+    jobs, objs = [], []
+    for f in src:
+        objs.append(os.path.join(d, os.path.basename(f) + ".o"))
+        jobs.append(subprocess.Popen([CLANG, "-O1", "-std=c++17", "-w", "-I" + os.path.join(ROOT, "tests", "host_hip"),
+                                      "-c", f, "-o", objs[-1]]))
+    oracle = os.path.join(d, "oracle.o")
+    subprocess.check_call(["gcc", "-O2", "-c", os.path.join(ROOT, "oracle", "cb_oracle.c"), "-o", oracle])
+    assert all(j.wait() == 0 for j in jobs)
+    exe = os.path.join(d, "windowed_lds")
+    subprocess.check_call([CLANG, *objs, oracle, "-o", exe, "-lpthread", "-lm"])
+    return exe
+
+
+def run(driver, cases):
+    """The driver's line for each case: all "ok"."""
+    r = subprocess.run([driver], input="\n".join(cases) + "\n", capture_output=True, text=True, timeout=600)
+    lines = r.stdout.split("\n")[:-1]
+    assert r.returncode == 0 and len(lines) == len(cases), r.stdout[-3000:] + r.stderr[-3000:]
+    for ln in lines:
+        assert ln.startswith("ok "), ln
+    return lines
+
+
+# Launches, then r and n of the items.  Lanes of two sizes whose window table has
+# more words than the item's workgroup has threads, beside a wider workgroup;
+# lanes of one size (another instance, another launch); tables that fit.
+MIXED = [(1, 2, 125, 613), (1, 2, 126, 500), (1, 2, 143, 613), (1, 2, 159, 613), (1, 3, 250, 500), (2, 2, 128, 613),
+         (1, 2, 613, 125), (2, 2, 125, 613, 45), (1, 1, 401, 613)]
+
+
+@pytest.mark.parametrize("form", [1, 2], ids=["per_tile", "queue"])
+def test_batches_of_unlike_workgroups(driver, form):
+    """One launch for the items of an instance, each item right, in both forms of a batch."""
+    cases = ["%d %d " % (form, len(n)) + " ".join("%d %d %d %d 2 1 %d" % (r, m, 1 + form % 2, 5 + k, 3 * (k < 2))
+                                                  for k, m in enumerate(n)) for _, r, *n in MIXED]
+    for ln, case in zip(run(driver, cases), MIXED):
+        assert "windowed=%d " % case[0] in ln, (case, ln)
