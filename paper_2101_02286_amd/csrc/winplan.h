@@ -284,6 +284,9 @@ bool build_window(int n, int R, const double *bands, bool cyclic, int M, double 
   const bool whole = cyclic && !ring && D >= L / 2;
   if (whole) D = std::max(1, L / 2);
   if (D > kWinMaxD) return false;
+  // (nor does an acyclic line's reach further than its lanes: a launch exchanges
+  // the values of L lanes, and slots beyond them hold nothing)
+  if (!cyclic) D = std::min(D, L - 1);
   w.M = M;
   w.L = L;
   w.base = base;

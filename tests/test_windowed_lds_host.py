@@ -1,6 +1,6 @@
 """What the windowed-lane kernels read of LDS, on the host with LDS that holds NaN
 until it is written (tests/windowed_lds_host.cpp): batches whose items have
-workgroups of different sizes, in both forms."""
+workgroups of different sizes, in both forms, and acyclic lines."""
 import os
 import subprocess
 
@@ -54,3 +54,16 @@ def test_batches_of_unlike_workgroups(driver, form):
                                                   for k, m in enumerate(n)) for _, r, *n in MIXED]
     for ln, case in zip(run(driver, cases), MIXED):
         assert "windowed=%d " % case[0] in ln, (case, ln)
+
+
+# short acyclic lines, whose window would be wider than the line, and longer ones
+ACYCLIC = [(1, 22), (1, 24), (1, 32), (1, 40), (1, 44), (1, 60), (2, 24), (2, 32), (2, 45), (2, 60), (2, 63), (2, 64),
+           (2, 72), (2, 128), (3, 32), (3, 64), (3, 80)]
+
+
+@pytest.mark.parametrize("axis", [1, 2])
+def test_acyclic_lines(driver, axis):
+    """Single calls, and pairs of such lines in one batch: each on a windowed kernel."""
+    lines = run(driver, ["0 1 %d %d %d 9 3 0 0" % (r, n, axis) for r, n in ACYCLIC])
+    assert all("windowed=1 " in ln for ln in lines)
+    run(driver, ["1 2 %d %d %d 9 3 0 0 %d %d %d 5 2 0 0" % (r, n, axis, r, n, axis) for r, n in ACYCLIC])
