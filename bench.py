@@ -68,14 +68,24 @@ def measured_traffic(group):
     return int(float(v)) if v else None
 
 
+def windowed_rows(plan, axis):
+    """Rows per lane of the windowed lanes that launches along `axis` run on, or 0 (the general kernels)."""
+    w = plan.array(13, 0 if axis == 0 else 1)
+    return int(w[0]) if len(w) else 0
+
+
+def lane_rows(plan, axis):
+    """Rows per lane of the kernel that launches along `axis` run on."""
+    return windowed_rows(plan, axis) or plan.info()["rows_per_lane" + ("" if axis == 0 else "_strided")]
+
+
 def kernel_group(plan, axis):
-    """Name of the line-kernel instance a launch along `axis` uses (unit-stride or strided layout)."""
-    i = plan.info()
-    if axis == 0:
-        return "unit-stride/r%d/rows%d/%s" % (i["r"], i["rows_per_lane"],
-                                              "elim" if i["interior_elimination"] else "pcr")
-    return "strided/r%d/rows%d/%s" % (i["r"], i["rows_per_lane_strided"],
-                                      "elim" if i["interior_elimination_strided"] else "pcr")
+    """Name of the kernel instance a launch along `axis` uses (unit-stride or strided layout)."""
+    name = "%s/r%d/rows%d" % ("unit-stride" if axis == 0 else "strided", plan.r, lane_rows(plan, axis))
+    if windowed_rows(plan, axis):
+        return "k_win " + name
+    elim = plan.info()["interior_elimination" + ("" if axis == 0 else "_strided")]
+    return "k_line %s/%s" % (name, "elim" if elim else "pcr")
 
 
 def scheme_stencil(name, n):
@@ -187,9 +197,7 @@ def headline(args):
         "config": {"workload": "%d^3 periodic grid, sixth-order compact first derivative (cyclic tridiagonal "
                                "alpha=1/3) fused with its stencil, along x, y, z" % n,
                    "n": n, "lines_per_direction": n * n, "partitions": 1,
-                   "launch": {k: {"rows_per_lane": (p.info()["rows_per_lane"] if k == "x"
-                                                    else p.info()["rows_per_lane_strided"])}
-                              for k, p in zip("xyz", plans)},
+                   "launch": {k: {"rows_per_lane": lane_rows(p, ax)} for ax, (k, p) in enumerate(zip("xyz", plans))},
                    "autotuned": tuned},
         "per_direction_ms": {k: round(float(v), 4) for k, v in zip("xyz", per_dir_ms)},
         "per_direction_gdofs": {k: round(dof / (float(v) * 1e-3) / 1e9, 2) for k, v in zip("xyz", per_dir_ms)},
@@ -202,8 +210,7 @@ def headline(args):
                               for k, c, v in zip("xyz", copy_ms, per_dir_ms)},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": measured_traffic(dom),
-                     "kernel": "%s %s (%s)" % ("k_win" if "strided" in dom and not tuned else "k_line", dom,
-                                            ", ".join("xyz"[ax] for ax in groups[dom])),
+                     "kernel": "%s (%s)" % (dom, ", ".join("xyz"[ax] for ax in groups[dom])),
                      "avg_launch_ms": round(dom_ms, 4), "bytes_per_launch": BYTES_PER_DOF * dof,
                      "copy_same_pattern_gbs": round(BYTES_PER_DOF * dof / (dom_copy_ms * 1e-3) / 1e9, 1),
                      "frac_of_copy_same_pattern": round(dom_copy_ms / dom_ms, 4)},

@@ -331,6 +331,10 @@ cb_status cb_plan_get_schedule(cb_plan_t plan, int32_t *out, int32_t cap, int32_
  *  12 boundary rows of D_i^{-1} [P][2][r][boundary_window]: rows 0..r-1 over
  *     the block's first boundary_window rows, then rows N_i-r..N_i-1 over
  *     its last boundary_window rows
+ *  13 windowed lanes of unit-stride (seg 0) or strided (seg 1) launches: rows
+ *     per lane, lanes, rows of the shorter lanes, lanes with one row more,
+ *     window half-width, 1 when every lane has coefficients of its own; empty
+ *     when the plan has none
  * Writes min(cap, size) values; *len receives the full size. */
 cb_status cb_plan_get_array(cb_plan_t plan, int32_t seg, int32_t which, double *out, int64_t cap,
                             int64_t *len);

@@ -1537,8 +1537,11 @@ cb_status cb_plan_get_schedule(cb_plan_t plan, int32_t *out, int32_t cap, int32_
 cb_status cb_plan_get_array(cb_plan_t plan, int32_t seg, int32_t which, double *out, int64_t cap, int64_t *len) {
   if (!plan || !len) return fail(CB_ERR_INVALID_ARG, "plan and len must be non-NULL");
   const Plan &p = plan->p;
-  if (seg < 0 || seg >= (int32_t)p.segs.size()) return fail(CB_ERR_INVALID_ARG, "segment index out of range");
-  const SegPlan &s = p.segs[seg];
+  const bool windows = which == 13 && (seg == 0 || seg == 1);
+  if (!windows && (seg < 0 || seg >= (int32_t)p.segs.size()))
+    return fail(CB_ERR_INVALID_ARG, "segment index out of range");
+  const SegPlan &s = p.segs[windows ? 0 : seg];
+  const WinLayout &w = seg == 0 ? p.wx : p.ws;
   std::vector<double> v;
   switch (which) {
     case 0: v = s.coef; break;
@@ -1556,6 +1559,9 @@ cb_status cb_plan_get_array(cb_plan_t plan, int32_t seg, int32_t which, double *
                   (double)s.ilu, (double)s.uniform, (double)s.cyclic};
       break;
     case 12: v = p.bfun; break;
+    case 13:
+      if (w.M) v = {(double)w.M, (double)w.L, (double)w.base, (double)w.extra, (double)w.D, (double)w.rows};
+      break;
     default: return fail(CB_ERR_INVALID_ARG, "unknown array id");
   }
   *len = (int64_t)v.size();
