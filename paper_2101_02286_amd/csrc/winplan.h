@@ -224,10 +224,10 @@ bool build_window(int n, int R, const double *bands, bool cyclic, int M, double 
       for (int i = 0; i < R; ++i) row[R + q] += rs.Ut.v[q * R + i] * wf[(size_t)i * N + j];
     }
     row[3 * R] = dinv[j];
-    for (int q = 0; q < RW; ++q)
-      if (q != 3 * R) biggest = std::max(biggest, std::fabs(row[q]));
+    for (int q = 0; q < RW; ++q)  // (ell alone grows with the bands' scale)
+      if (q != 3 * R) biggest = std::max(biggest, std::fabs(row[q]) / (q / R == 2 ? scale : 1.0));
   }
-  if (!(biggest <= 64.0 * std::max(1.0, scale))) return false;  // elimination that grows needs pivoting
+  if (!(biggest <= 64.0)) return false;  // elimination that grows needs pivoting
   for (int ty = 0; ty < 2; ++ty) {
     const int m = ty == 0 || !two ? N : N - 1;  // interior rows of this lane size
     // z: L~ times the last R rows of U^{-1}, on the last R values of z
@@ -351,6 +351,10 @@ bool build_window(int n, int R, const double *bands, bool cyclic, int M, double 
       continue;
     }
     if (!inverse_row(rs, l, K, g)) return w.M = 0, false;
+    // (rows near the ends of an acyclic line, or between lanes of two sizes)
+    double sum = 0.0, out = 0.0;
+    for (int d = -K; d <= K; ++d) (std::abs(d) > D ? out : sum) += abs_sum(g[K + d], R);
+    if (!(out <= tol * (sum + out))) return w.M = 0, false;
     const int at = (int)seen.size();
     seen[key] = at;
     w.gidx[l] = at;
@@ -370,6 +374,9 @@ bool build_window_rows(int n, int R, const double *bands, bool cyclic, int M, do
   auto start = [&](int l) { return l * base + std::min(l, extra); };
   auto wrap = [&](int l) { return l < 0 ? l + L : (l >= L ? l - L : l); };
   auto rows_of = [&](int l) { return base + (l < extra ? 1 : 0) - R; };  // interior
+  std::vector<double> top(n, 0.0);  // largest entry of each row: what is small or large is so beside it
+  for (int j = 0; j < n; ++j)
+    for (int o = -R; o <= R; ++o) top[j] = std::max(top[j], std::fabs(a(j, o)));
   std::vector<Blk> Sf(L), Sl(L), Rf(L), Rl(L), Lt(L), Dt(L), Ut(L);
   w.coef.assign((size_t)L * win_lane_size(R, M), 0.0);
   for (int l = 0; l < L; ++l) {
@@ -385,10 +392,8 @@ bool build_window_rows(int n, int R, const double *bands, bool cyclic, int M, do
     for (int j = 0; j < m; ++j)
       for (int o = -R; o <= R; ++o) c[(size_t)j * W + o + R] = j + o < 0 ? 0.0 : a(g0 + j, o);
     for (int j = 0; j < m; ++j) {
-      double scale = 0.0;
-      for (int o = -R; o <= R; ++o) scale = std::max(scale, std::fabs(a(g0 + j, o)));
       const double piv = c[(size_t)j * W + R];
-      if (!(std::fabs(piv) > 1e-2 * scale) || !std::isfinite(piv)) return false;
+      if (!(std::fabs(piv) > 1e-2 * top[g0 + j]) || !std::isfinite(piv)) return false;
       dinv[j] = 1.0 / piv;
       for (int i = j + 1; i <= std::min(m - 1, j + R); ++i) {
         const double f = c[(size_t)i * W + (j - i + R)] / piv;
@@ -435,7 +440,8 @@ bool build_window_rows(int n, int R, const double *bands, bool cyclic, int M, do
         Rl[l].v[i * R + s] = x[m - R + i];
       }
     }
-    double biggest = 0.0, top = 1.0;
+    bool bounded = true;  // the factors of the lane's rows, each of these divided by its largest entry
+    auto note = [&](double v, double by) { bounded = bounded && std::fabs(v) <= 64.0 * by; };
     for (int j = 0; j < m; ++j) {
       double *t = row + (size_t)j * RW;
       for (int q = 0; q < R; ++q) {
@@ -444,11 +450,14 @@ bool build_window_rows(int n, int R, const double *bands, bool cyclic, int M, do
         for (int i = 0; i < R; ++i) t[R + q] += Ut[l].v[q * R + i] * wf[(size_t)i * m + j];
       }
       t[3 * R] = dinv[j];
-      for (int q = 0; q < RW; ++q)
-        if (q != 3 * R) biggest = std::max(biggest, std::fabs(t[q]));
-      for (int o = -R; o <= R; ++o) top = std::max(top, std::fabs(a(g0 + j, o)));
+      for (int q = 0; q < R; ++q) {
+        if (q < j) note(t[q], top[g0 + j] / top[g0 + j - q - 1]);
+        note(t[R + q], top[i0 + q] / top[g0 + j]);
+        note(t[2 * R + q], top[g0 + j]);
+        note(t[3 * R + 1 + q], 1.0);
+      }
     }
-    if (!(biggest <= 64.0 * top)) return false;  // elimination that grows needs pivoting
+    if (!bounded) return false;  // elimination that grows needs pivoting
     // z: the next lane's L~ times the last R rows of U^{-1}, on the last R values of z
     const int nx = wrap(l + 1), ni = start(nx);
     for (int i = 0; i < R; ++i) {
@@ -480,7 +489,17 @@ bool build_window_rows(int n, int R, const double *bands, bool cyclic, int M, do
       }
   }
   for (int i = 0; i < n * W; ++i) scale = std::max(scale, std::fabs(bands[i]));
+  // rows of like size by powers of two, which a pivot search among them needs
+  std::vector<double> unit(m);
+  for (int i = 0; i < m; ++i) {
+    double big = 0.0;
+    for (int j = 0; j < m; ++j) big = std::max(big, std::fabs(t[(size_t)i * m + j]));
+    unit[i] = big > 0.0 && std::isfinite(big) ? std::ldexp(1.0, -std::ilogb(big)) : 1.0;
+    for (int j = 0; j < m; ++j) t[(size_t)i * m + j] *= unit[i];
+  }
   if (!invert(m, t.data(), inv.data())) return false;
+  for (int i = 0; i < m; ++i)
+    for (int j = 0; j < m; ++j) inv[(size_t)i * m + j] *= unit[j];
   // the narrowest window that leaves out no more than tol of any lane's row
   auto dist = [&](int l, int j) {
     int d = j - l;
@@ -491,18 +510,19 @@ bool build_window_rows(int n, int R, const double *bands, bool cyclic, int M, do
   int D = 1;
   for (int l = 0; l < L; ++l) {
     std::vector<double> far(L + 1, 0.0);
-    double sum = 0.0;
+    double sum = 0.0, weight = 0.0;
     for (int j = 0; j < L; ++j)
       for (int i = 0; i < R; ++i)
         for (int c = 0; c < R; ++c) {
           const double v = std::fabs(inv[(size_t)(l * R + i) * m + j * R + c]);
-          far[std::abs(dist(l, j))] += v;
+          far[std::abs(dist(l, j))] += v * top[start(j) + c];
+          weight += v * top[start(j) + c];
           sum += v;
         }
     if (!std::isfinite(sum) || !(sum * scale <= 1e4)) return false;
     double out = 0.0;
     int d = L;
-    while (d > 0 && out + far[d] <= tol * sum) out += far[d--];
+    while (d > 0 && out + far[d] <= tol * weight) out += far[d--];
     D = std::max(D, d);
   }
   if (D > kWinMaxD || D > L - 1) return false;

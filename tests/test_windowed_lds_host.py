@@ -1,6 +1,7 @@
 """What the windowed-lane kernels read of LDS, on the host with LDS that holds NaN
 until it is written (tests/windowed_lds_host.cpp): batches whose items have
-workgroups of different sizes, in both forms, and acyclic lines."""
+workgroups of different sizes, in both forms, acyclic
+lines, and rows of unlike scale."""
 import os
 import subprocess
 
@@ -67,3 +68,10 @@ def test_acyclic_lines(driver, axis):
     lines = run(driver, ["0 1 %d %d %d 9 3 0 0" % (r, n, axis) for r, n in ACYCLIC])
     assert all("windowed=1 " in ln for ln in lines)
     run(driver, ["1 2 %d %d %d 9 3 0 0 %d %d %d 5 2 0 0" % (r, n, axis, r, n, axis) for r, n in ACYCLIC])
+
+
+@pytest.mark.parametrize("n", [39, 44, 66, 88, 128, 130, 200])
+def test_rows_of_unlike_scale(driver, n):
+    """Per-row bands, half of them scaled with their right-hand side: as exact as without."""
+    lines = run(driver, ["0 1 1 %d %d 5 2 %d 0" % (n, axis, c) for axis in (1, 2) for c in (2, 3)])
+    assert any("windowed=1 " in ln for ln in lines)
