@@ -451,17 +451,7 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
       // window half-width 3: 115 GDOF/s with 4, 180 with 8; n = 701 tridiagonal
       // 185 with 4, 254 with 8); the general kernel below four (n = 1000
       // heptadiagonal 77 against 29)
-      const size_t table = wl.g.size() + wl.coef.size();
-      const size_t wave = (size_t)a.lpw * ((size_t)w.k->lds * (a.Lw + 2 * a.D + 2) + 2 * ((a.Lw * (wl.M + 1) + 2 * QP + 4) & ~1));
-      int most = 0;
-      for (int v : {4, 8, 7, 6, 5, 3, 2, 1}) {
-        const int on = std::min<int>(8, v * (int)(lds_cap() / ((table + v * wave) * sizeof(double))));
-        if (on > most) {
-          most = on;
-          waves = v;
-        }
-      }
-      if (most < 4) return false;
+      if (win_rows_waves(p.R, wl.M, wl.L, wl.D, QP, lds_cap(), &waves) < kWinRowsWaves) return false;
       w.threads = 64 * waves;
     }
     a.W = waves * a.lpw;

@@ -15,6 +15,7 @@
 #include <cstring>
 #include <functional>
 #include <initializer_list>
+#include <map>
 
 namespace cb {
 namespace {
@@ -941,11 +942,27 @@ static void choose_windows(const cb_plan_desc &d, Plan &p) {
   const int parts = d.partitions > 1 ? d.partitions : 0;
   const double tol = std::ldexp(1.0, -57);
   if (d.per_row) {
-    auto rows = [&](std::initializer_list<int> order, WinLayout &w) {
-      for (int M : order)
-        if (M && !w.M && !build_window_rows(n, R, p.bands.data(), cyclic, M, tol, w)) w = WinLayout();
-    };
     if (parts) return;
+    std::map<int, WinLayout> built;  // by rows per lane (M = 0: refused), for either row stride
+    // unit stride: does a compute unit hold enough wavefronts of M-row lanes (at the narrowest window, if not known)
+    auto fits = [&](int M, int D) {
+      const int L = (n + M - 1) / M;
+      int waves;
+      return L > 64 || win_rows_waves(R, M, L, D, 0, kWinLds, &waves) >= kWinRowsWaves;
+    };
+    auto rows = [&](std::initializer_list<int> order, WinLayout &w) {
+      for (int M : order) {
+        if (!M || w.M) continue;
+        if (&w == &p.wx && !fits(M, 1)) return;
+        auto it = built.find(M);
+        if (it == built.end()) {
+          it = built.emplace(M, WinLayout()).first;
+          if (!build_window_rows(n, R, p.bands.data(), cyclic, M, tol, it->second)) it->second = WinLayout();
+        }
+        w = it->second;
+      }
+      if (&w == &p.wx && w.M && !fits(w.M, w.D)) w = WinLayout();
+    };
     const int by12 = n % 12 == 0 ? 12 : 0, by16 = n % 16 == 0 ? 16 : 0;
     if (R == 1 && n > 128 && (by12 || n > 256 || !p.segs[0].uniform))
       rows({by12, n % 8 == 0 && n <= 512 ? 8 : 0, 12, 16, 8}, p.wx);

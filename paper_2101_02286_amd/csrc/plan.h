@@ -122,6 +122,26 @@ struct WinLayout {
 constexpr int win_row_size(int R) { return 4 * R + 1; }
 constexpr int win_lane_size(int R, int M) { return ((M - R) * win_row_size(R) + R * R) | 1; }
 constexpr int kWinMaxD = 8;  // widest window the kernels take
+constexpr size_t kWinLds = 163840;  // LDS of a gfx950 compute unit
+
+// Wavefronts (up to two per SIMD) that a compute unit holds of unit-stride
+// launches of lanes with coefficients of their own: workgroups of `waves`
+// wavefronts share a copy of the lanes' tables, and each wavefront takes the
+// exchange planes and the tile of 64 / L pairs of lines with QP halo rows.
+inline int win_rows_waves(int R, int M, int L, int D, int QP, size_t lds, int *waves) {
+  const size_t table = (size_t)L * (win_lane_size(R, M) + (2 * D + 1) * R * R);
+  const size_t wave = (size_t)(64 / L) * (4 * R * (L + 2 * D + 2) + 2 * ((L * (M + 1) + 2 * QP + 4) & ~1));
+  int most = 0;
+  for (int v : {4, 8, 7, 6, 5, 3, 2, 1}) {
+    const int each = v * (int)(lds / ((table + v * wave) * sizeof(double))), on = each < 8 ? each : 8;
+    if (on > most) {
+      most = on;
+      *waves = v;
+    }
+  }
+  return most;
+}
+constexpr int kWinRowsWaves = 4;  // fewer than these and the general kernel is faster
 
 // Device view of a segment plan (POD, passed inside kernel arguments).
 struct SegDev {

@@ -140,6 +140,110 @@ bool inverse_row(const Reduced &rs, int l, int K, std::vector<Blk> &g) {
   return true;
 }
 
+// A block tridiagonal matrix of L >= 2 blocks, with corners when cyclic (lo[0]
+// multiplies the last lane's unknowns, up[L-1] the first's).
+struct BlockRing {
+  int L, R;
+  bool cyclic;
+  std::vector<Blk> lo, di, up;
+};
+
+// Its inverse [L][L][R][R], by elimination among all rows: O(L^3 R^3).
+bool invert_dense(const BlockRing &a, std::vector<double> &inv) {
+  const int L = a.L, R = a.R, m = L * R;
+  std::vector<double> t((size_t)m * m, 0.0), x((size_t)m * m);
+  for (int l = 0; l < L; ++l) {
+    const int lm = l > 0 ? l - 1 : L - 1, lp = l + 1 < L ? l + 1 : 0;
+    for (int i = 0; i < R; ++i)
+      for (int c = 0; c < R; ++c) {
+        t[(size_t)(l * R + i) * m + lm * R + c] += a.lo[l].v[i * R + c];
+        t[(size_t)(l * R + i) * m + l * R + c] += a.di[l].v[i * R + c];
+        t[(size_t)(l * R + i) * m + lp * R + c] += a.up[l].v[i * R + c];
+      }
+  }
+  if (!invert(m, t.data(), x.data())) return false;
+  inv.resize((size_t)m * m);
+  for (int i = 0; i < m; ++i)
+    for (int j = 0; j < m; ++j) inv[(((size_t)(i / R) * L + j / R) * R + i % R) * R + j % R] = x[(size_t)i * m + j];
+  return true;
+}
+
+// The same by block elimination from the first block, the last being a border
+// of a cyclic matrix: O(L^2 R^3), and most matrices here need no pivoting among
+// blocks.  False where it loses digits (a residual above 2^-46).
+template <int R>
+bool invert_blocks(const BlockRing &a, std::vector<double> &inv) {
+  struct Mat {
+    double v[R * R];
+    Mat operator*(const Mat &b) const {
+      Mat c;
+      for (int i = 0; i < R; ++i)
+        for (int j = 0; j < R; ++j) {
+          c.v[i * R + j] = 0.0;
+          for (int k = 0; k < R; ++k) c.v[i * R + j] += v[i * R + k] * b.v[k * R + j];
+        }
+      return c;
+    }
+    Mat plus(const Mat &b, double f) const {
+      Mat c;
+      for (int i = 0; i < R * R; ++i) c.v[i] = v[i] + f * b.v[i];
+      return c;
+    }
+  };
+  const int L = a.L, last = L - 1;
+  const int T = a.cyclic ? L - 1 : L;  // blocks of the tridiagonal part
+  std::vector<Mat> lo(L), di(L), up(L);
+  for (int i = 0; i < L; ++i)
+    for (int q = 0; q < R * R; ++q) {
+      lo[i].v[q] = a.lo[i].v[q];
+      di[i].v[q] = a.di[i].v[q];
+      up[i].v[q] = a.up[i].v[q];
+    }
+  const Mat zero{};
+  std::vector<Mat> w(T), f(T);  // inverses of the eliminated diagonal blocks; lo w of the block before
+  for (int i = 0; i < T; ++i) {
+    f[i] = i > 0 ? lo[i] * w[i - 1] : zero;
+    const Mat d = i > 0 ? di[i].plus(f[i] * up[i - 1], -1.0) : di[i];
+    if (!invert(R, d.v, w[i].v)) return false;
+  }
+  std::vector<Mat> x((size_t)L * L, zero);  // columns one after the other
+  auto at = [&](int i, int j) -> Mat & { return x[(size_t)j * L + i]; };
+  for (int j = 0; j < T; ++j) {
+    for (int i = 0; i < R; ++i) at(j, j).v[i * R + i] = 1.0;
+    for (int i = j + 1; i < T; ++i) at(i, j) = zero.plus(f[i] * at(i - 1, j), -1.0);
+    for (int i = T - 1; i >= 0; --i) at(i, j) = w[i] * (i + 1 < T ? at(i, j).plus(up[i] * at(i + 1, j), -1.0) : at(i, j));
+  }
+  if (a.cyclic) {
+    std::vector<Mat> tb(T), ct(T);  // the inverse so far times the border's column; its row times the inverse
+    for (int i = 0; i < T; ++i) {
+      tb[i] = (at(i, 0) * lo[0]).plus(at(i, T - 1) * up[T - 1], 1.0);
+      ct[i] = (lo[last] * at(T - 1, i)).plus(up[last] * at(0, i), 1.0);
+    }
+    const Mat schur = di[last].plus(lo[last] * tb[T - 1], -1.0).plus(up[last] * tb[0], -1.0);
+    if (!invert(R, schur.v, at(last, last).v)) return false;
+    for (int i = 0; i < T; ++i) {
+      at(i, last) = zero.plus(tb[i] * at(last, last), -1.0);
+      at(last, i) = zero.plus(at(last, last) * ct[i], -1.0);
+    }
+    for (int j = 0; j < T; ++j)
+      for (int i = 0; i < T; ++i) at(i, j) = at(i, j).plus(at(i, last) * ct[j], -1.0);
+  }
+  inv.resize((size_t)L * L * R * R);
+  double worst = 0.0;  // of A inv - 1
+  for (int j = 0; j < L; ++j)
+    for (int i = 0; i < L; ++i) {
+      std::copy(at(i, j).v, at(i, j).v + R * R, inv.begin() + ((size_t)i * L + j) * R * R);
+      Mat e = di[i] * at(i, j);
+      if (a.cyclic || i > 0) e = e.plus(lo[i] * at(i > 0 ? i - 1 : last, j), 1.0);
+      if (a.cyclic || i < last) e = e.plus(up[i] * at(i < last ? i + 1 : 0, j), 1.0);
+      for (int q = 0; q < R * R; ++q) {
+        const double r = std::fabs(e.v[q] - (i == j && q / R == q % R ? 1.0 : 0.0));
+        worst = r <= worst ? worst : r;  // (NaN stays)
+      }
+    }
+  return worst <= std::ldexp(1.0, -46);
+}
+
 }  // namespace window
 
 bool build_window(int n, int R, const double *bands, bool cyclic, int M, double tol, bool ring, WinLayout &w) {
@@ -304,28 +408,21 @@ bool build_window(int n, int R, const double *bands, bool cyclic, int M, double 
     return true;
   }
   if (cyclic && L < 2 * K + 2) {  // few lanes: the dense inverse
-    const int m = L * R;
-    std::vector<double> t((size_t)m * m, 0.0), inv((size_t)m * m);
+    BlockRing ring{L, R, true, {}, {}, {}};
     for (int l = 0; l < L; ++l) {
-      const int lm = rs.wrap(l - 1), lp = rs.wrap(l + 1);
-      const Blk lo = rs.lower(l), di = rs.diag(l), up = rs.upper(l);
-      for (int i = 0; i < R; ++i)
-        for (int c = 0; c < R; ++c) {
-          t[(size_t)(l * R + i) * m + lm * R + c] += lo.v[i * R + c];
-          t[(size_t)(l * R + i) * m + l * R + c] += di.v[i * R + c];
-          t[(size_t)(l * R + i) * m + lp * R + c] += up.v[i * R + c];
-        }
+      ring.lo.push_back(rs.lower(l));
+      ring.di.push_back(rs.diag(l));
+      ring.up.push_back(rs.upper(l));
     }
-    if (!invert(m, t.data(), inv.data())) return w.M = 0, false;
+    std::vector<double> inv;
+    if (!invert_dense(ring, inv)) return w.M = 0, false;
     const int rows = w.uniform ? 1 : L;
     for (int l = 0; l < rows; ++l) {
       std::vector<Blk> row(2 * D + 1);
       for (int d = -D; d <= D; ++d) {
         if (2 * D >= L && d == -D && L % 2 == 0) continue;  // lane l - L/2 is lane l + L/2
         if (d < -((L - 1) / 2) || d > L / 2) continue;
-        const int j = rs.wrap(l + d);
-        for (int i = 0; i < R; ++i)
-          for (int c = 0; c < R; ++c) row[D + d].v[i * R + c] = inv[(size_t)(l * R + i) * m + j * R + c];
+        std::copy_n(inv.begin() + ((size_t)l * L + rs.wrap(l + d)) * RR, RR, row[D + d].v);
       }
       put(row, D);
       w.gidx[l] = l;
@@ -468,38 +565,35 @@ bool build_window_rows(int n, int R, const double *bands, bool cyclic, int M, do
         for (int s = 0; s < R; ++s) row[(size_t)(M - R) * RW + b * R + i] += a(ni + b, s - R - b) * x[m - R + s];
     }
   }
-  // the reduced system (Eqs. (18)-(20)) and its dense inverse
-  const int m = L * R;
-  std::vector<double> t((size_t)m * m, 0.0), inv((size_t)m * m);
+  // the reduced system (Eqs. (18)-(20)) and its inverse; its rows are brought to
+  // one size by powers of two, which the pivot search in a block needs
   double scale = 0.0;
+  BlockRing ring{L, R, cyclic, std::vector<Blk>(L), std::vector<Blk>(L), std::vector<Blk>(L)};
+  std::vector<Blk> &lo = ring.lo, &di = ring.di, &up = ring.up;
+  std::vector<double> unit(L * R), inv;
   for (int l = 0; l < L; ++l) {
-    const int lm = wrap(l - 1), lp = wrap(l + 1);
-    const bool first = !cyclic && l == 0, last = !cyclic && l == L - 1;
-    Blk di = sub(Dt[l], mul(Ut[l], Sf[l], R), R), lo, up;
-    if (!first) {
-      di = sub(di, mul(Lt[l], Rl[lm], R), R);
-      lo = neg(mul(Lt[l], Sl[lm], R), R);
+    di[l] = sub(Dt[l], mul(Ut[l], Sf[l], R), R);
+    if (cyclic || l > 0) {
+      di[l] = sub(di[l], mul(Lt[l], Rl[wrap(l - 1)], R), R);
+      lo[l] = neg(mul(Lt[l], Sl[wrap(l - 1)], R), R);
     }
-    if (!last) up = neg(mul(Ut[l], Rf[l], R), R);
-    for (int i = 0; i < R; ++i)
-      for (int c = 0; c < R; ++c) {
-        t[(size_t)(l * R + i) * m + lm * R + c] += lo.v[i * R + c];
-        t[(size_t)(l * R + i) * m + l * R + c] += di.v[i * R + c];
-        t[(size_t)(l * R + i) * m + lp * R + c] += up.v[i * R + c];
-      }
+    if (cyclic || l < L - 1) up[l] = neg(mul(Ut[l], Rf[l], R), R);
+    for (int i = 0; i < R; ++i) {
+      double big = 0.0;
+      for (const Blk *b : {&lo[l], &di[l], &up[l]})
+        for (int c = 0; c < R; ++c) big = std::max(big, std::fabs(b->v[i * R + c]));
+      const double u = big > 0.0 && std::isfinite(big) ? std::ldexp(1.0, -std::ilogb(big)) : 1.0;
+      unit[l * R + i] = u;
+      for (Blk *b : {&lo[l], &di[l], &up[l]})
+        for (int c = 0; c < R; ++c) b->v[i * R + c] *= u;
+    }
   }
   for (int i = 0; i < n * W; ++i) scale = std::max(scale, std::fabs(bands[i]));
-  // rows of like size by powers of two, which a pivot search among them needs
-  std::vector<double> unit(m);
-  for (int i = 0; i < m; ++i) {
-    double big = 0.0;
-    for (int j = 0; j < m; ++j) big = std::max(big, std::fabs(t[(size_t)i * m + j]));
-    unit[i] = big > 0.0 && std::isfinite(big) ? std::ldexp(1.0, -std::ilogb(big)) : 1.0;
-    for (int j = 0; j < m; ++j) t[(size_t)i * m + j] *= unit[i];
-  }
-  if (!invert(m, t.data(), inv.data())) return false;
-  for (int i = 0; i < m; ++i)
-    for (int j = 0; j < m; ++j) inv[(size_t)i * m + j] *= unit[j];
+  const bool done = R == 1 ? invert_blocks<1>(ring, inv) : (R == 2 ? invert_blocks<2>(ring, inv) : invert_blocks<3>(ring, inv));
+  if (!done && !invert_dense(ring, inv)) return false;
+  for (int l = 0; l < L; ++l)
+    for (int j = 0; j < L; ++j)
+      for (int i = 0; i < RR; ++i) inv[((size_t)l * L + j) * RR + i] *= unit[j * R + i % R];
   // the narrowest window that leaves out no more than tol of any lane's row
   auto dist = [&](int l, int j) {
     int d = j - l;
@@ -514,7 +608,7 @@ bool build_window_rows(int n, int R, const double *bands, bool cyclic, int M, do
     for (int j = 0; j < L; ++j)
       for (int i = 0; i < R; ++i)
         for (int c = 0; c < R; ++c) {
-          const double v = std::fabs(inv[(size_t)(l * R + i) * m + j * R + c]);
+          const double v = std::fabs(inv[((size_t)l * L + j) * RR + i * R + c]);
           far[std::abs(dist(l, j))] += v * top[start(j) + c];
           weight += v * top[start(j) + c];
           sum += v;
@@ -539,9 +633,7 @@ bool build_window_rows(int n, int R, const double *bands, bool cyclic, int M, do
     for (int j = 0; j < L; ++j) {
       const int d = dist(l, j);
       if (std::abs(d) > D) continue;
-      for (int i = 0; i < R; ++i)
-        for (int c = 0; c < R; ++c)
-          w.g[((size_t)l * (2 * D + 1) + D + d) * RR + i * R + c] = inv[(size_t)(l * R + i) * m + j * R + c];
+      std::copy_n(inv.begin() + ((size_t)l * L + j) * RR, RR, w.g.begin() + ((size_t)l * (2 * D + 1) + D + d) * RR);
     }
   }
   return true;
