@@ -1,6 +1,7 @@
 """Autotuner for the line-solver launch shape.
 
-For one (bands, n, precision, grid shape, axis) it times every valid choice of
+For one (bands, n, precision, grid shape, axis) it times the automatic plan (the
+only one that may run windowed lanes) and every valid choice of
   * partitions    -- workgroups per line (the two-level split of Sec. 3-4 with
     workgroups as partitions; FP64 lines of 1024 rows or more),
   * rows_per_lane -- where the reduction switches from registers (generalized
@@ -36,15 +37,17 @@ DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "cb_tune.json")
 
 
 def _key(bands, n, precision, shape, axis, fused):
-    return "r%d|n%d|%s|%s|ax%d|%s|%s" % ((len(bands) - 1) // 2, n, precision, "x".join(map(str, shape)), axis,
+    # (v2: the automatic plan is among the choices)
+    return "v2|r%d|n%d|%s|%s|ax%d|%s|%s" % ((len(bands) - 1) // 2, n, precision, "x".join(map(str, shape)), axis,
                                         "fused" if fused else "solve", ",".join("%.17g" % b for b in bands))
 
 
 PARTS = (2, 4, 8, 16)
+AUTOMATIC = dict(partitions=0, rows_per_lane=0, lines_per_wg=0, block_barriers=0, x_staging=0, interior=0, tile_order=0)
 
 
 def candidates(bands, n, precision, strided=None):
-    """Launch choices to time.  `strided` True: rows are strided (x_staging is
+    """Launch choices to time beside the automatic plan.  `strided` True: rows are strided (x_staging is
     moot; both tile orders are tried); False: unit-stride rows; None: both."""
     out = []
     xss = (0,) if strided else (1, 2)
@@ -79,6 +82,13 @@ def candidates(bands, n, precision, strided=None):
     return out
 
 
+def choices(bands, n, precision, strided=None, one_partition=False, max_candidates=None):
+    """What tune() times, in order: the automatic plan, then candidates()."""
+    out = [dict(AUTOMATIC, partitions=int(one_partition))]
+    out += [c for c in candidates(bands, n, precision, strided) if c["partitions"] == 1 or not one_partition]
+    return out[:max_candidates] if max_candidates else out
+
+
 def _time(fn, reps, stream):
     fn()
     torch.cuda.synchronize()
@@ -109,12 +119,7 @@ def tune(bands, n, f, axis, stencil=None, precision="fp64", refine_iters=0, reps
     stream = torch.cuda.current_stream()
     out = torch.empty_like(f)
     table = []
-    cands = candidates(bands, n, precision, strided=f.stride(2 - axis) != 1)
-    if one_partition:
-        cands = [c for c in cands if c["partitions"] == 1]
-    if max_candidates:
-        cands = cands[:max_candidates]
-    for c in cands:
+    for c in choices(bands, n, precision, f.stride(2 - axis) != 1, one_partition, max_candidates):
         try:
             p = cb.Plan(bands, n, precision=precision, refine_iters=refine_iters, **c)
         except cb.CbError:
@@ -131,8 +136,7 @@ def tune(bands, n, f, axis, stencil=None, precision="fp64", refine_iters=0, reps
         table.append(dict(c, ms=ms))
         p.close()
     best = min(table, key=lambda r: r["ms"])
-    best = {k: best[k] for k in ("partitions", "rows_per_lane", "lines_per_wg", "block_barriers", "x_staging",
-                                 "interior", "tile_order")}
+    best = {k: best[k] for k in AUTOMATIC}
     if cache:
         db[key] = {"best": best, "table": table}
         os.makedirs(os.path.dirname(cache), exist_ok=True)
