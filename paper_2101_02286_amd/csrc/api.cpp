@@ -105,6 +105,21 @@ int xcd_count() {
   return v;
 }
 
+// Compute units of the current device, queried once per device (256 if the query fails).
+int cu_count() {
+  static std::mutex mu;
+  static std::map<int, int> cache;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  std::lock_guard<std::mutex> lk(mu);
+  auto it = cache.find(dev);
+  if (it != cache.end()) return it->second;
+  int v = 0;
+  if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1) v = 256;
+  cache[dev] = v;
+  return v;
+}
+
 cb_status fail(cb_status s, const std::string &m) {
   g_err = m;
   return s;
@@ -1035,10 +1050,17 @@ cb_status cb_rhs_stencil(const cb_stencil *stencil, const cb_grid *grid, int32_t
     const int64_t ltiles = (g.nlines + s.W - 1) / s.W;
     w.blocks = ltiles * s.nch;
     s.ltiles = (uint32_t)ltiles;
-    if (w.blocks <= 0x7fffffff && w.lds <= lds_cap()) return launch_win(w, static_cast<hipStream_t>(stream));
+    // The one-point-per-thread kernel is faster where the tiles do not give every
+    // compute unit a workgroup (2^19 points: n = 100 4.7 against 5.4 us; 2^20 7.7 :
+    // 7.5), and on many lines of less than six lanes, whose tiles are full of bank
+    // conflicts and halo (n = 48 212 : 246 us at 2^25 points, n = 72 0.94-1.17 times as
+    // fast; lanes that divide a line of 64 rows 1.4-1.7)
+    const bool few = w.blocks < cu_count(), narrow = s.L < 6 && s.n != 64 && g.nlines > (int64_t)32 * cu_count();
+    if (!few && !narrow && w.blocks <= 0x7fffffff && w.lds <= lds_cap())
+      return launch_win(w, static_cast<hipStream_t>(stream));
   }
   // strided lines next to each other: pairs of them, 32-bit tile indices
-  int form = STENCIL_ANY;
+  int form = g.n < 3 ? STENCIL_TINY : STENCIL_ANY;
   if (a.rs != 1 && g.su == 1 && g.n < (1 << 30)) {
     int64_t nv = g.nlines / g.nu;
     if (g.sv == g.nu && g.nlines < (int64_t(1) << 31)) {  // one run across planes
@@ -1048,7 +1070,14 @@ cb_status cb_rhs_stencil(const cb_stencil *stencil, const cb_grid *grid, int32_t
     a.nt = a.rs % 16 == 0 && (nv == 1 || a.sv % 16 == 0) && (uintptr_t)b % 128 == 0;  // whole cache lines
     const int per = 4 * (a.nt ? kStencilRows / 2 : kStencilRows);
     const int64_t runs = (a.nu + 127) / 128, rows = (g.n + per - 1) / per;
-    if (a.nu < (int64_t(1) << 31) && runs * rows * nv < (int64_t(1) << 31)) {
+    // Tiles take 128 lines and `per` rows, and a wavefront its rows one after the
+    // other: worth it where a third of the tiles' points or more are the field's
+    // (rows of 2 lines in planes of their own 207 : 3094 us at 2^25 points, 24 225 :
+    // 281, 48 227 : 168) and enough wavefronts run at a time (128-line rows 4.6 : 6.9
+    // us at 2^19 points, 9.3 : 10.2 at 2^20, 17 : 11 at 2^21)
+    const double tiled = (double)runs * rows * nv * per * 128, share = (double)a.total / tiled;
+    const bool fills = 3 * share >= 1 && (double)a.total * share >= 6144.0 * cu_count();
+    if (fills && a.nu < (int64_t(1) << 31) && runs * rows * nv < (int64_t(1) << 31)) {
       form = a.nt ? STENCIL_S_SHORT : STENCIL_S;
       a.dq = make_divmagic((uint32_t)runs);
       a.du = make_divmagic((uint32_t)rows);

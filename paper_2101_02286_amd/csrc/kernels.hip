@@ -87,7 +87,10 @@ __global__ __launch_bounds__(256) void k_stencil_s(const StencilArgs a) {
   }
 }
 
-// Any positive strides and any size.
+// Any positive strides and any size: small fields, narrow rows and short lines.
+// TINY: lines shorter than the stencil's reach, whose taps wrap more than once (a
+// check of that in the one instance cost 5 %).
+template <bool TINY>
 __global__ __launch_bounds__(256) void k_stencil(const StencilArgs a) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= a.total) return;
@@ -109,8 +112,8 @@ __global__ __launch_bounds__(256) void k_stencil(const StencilArgs a) {
   double acc = 0.0;
   for (int q = a.lo; q <= a.hi; ++q) {
     int64_t jj = j + q;
-    while (jj < 0) jj += a.n;
-    while (jj >= a.n) jj -= a.n;
+    if (TINY) jj = (jj + 3 * a.n) % a.n;
+    else jj = jj < 0 ? jj + a.n : (jj >= a.n ? jj - a.n : jj);
     acc += a.c[q - a.lo] * a.f[base + jj * a.rs];
   }
   a.b[base + j * a.rs] = acc;
@@ -207,7 +210,8 @@ const WinKernel *find_win_kernel(int R, int M, int mode, int Q, bool uni) {
 const void *stencil_kernel(int form) {
   return form == STENCIL_S         ? (const void *)&k_stencil_s<kStencilRows>
          : form == STENCIL_S_SHORT ? (const void *)&k_stencil_s<kStencilRows / 2>
-                                   : (const void *)&k_stencil;
+         : form == STENCIL_TINY    ? (const void *)&k_stencil<true>
+                                   : (const void *)&k_stencil<false>;
 }
 
 const BatchKernel *find_batch_kernel(int R, int M, int fp32, bool uni, bool ilu, int mode, int Q) {

@@ -116,8 +116,8 @@ struct StencilArgs {
   double c[7];
 };
 // Forms of the stencil kernel: strided lines next to each other (workgroups of
-// 4 x kStencilRows rows, or half as many), anything.
-enum { STENCIL_ANY = 0, STENCIL_S = 1, STENCIL_S_SHORT = 2 };
+// 4 x kStencilRows rows, or half as many), anything, lines of less than three rows.
+enum { STENCIL_ANY = 0, STENCIL_S = 1, STENCIL_S_SHORT = 2, STENCIL_TINY = 3 };
 constexpr int kStencilRows = 16;
 
 struct LineKernel {
