@@ -13,6 +13,7 @@
 #include "../../include/cb.h"
 #include "launch.h"
 #include "plan.h"
+#include "route.h"
 
 struct cb_plan_s {
   cb::Plan p;
@@ -380,10 +381,37 @@ struct WinLaunch {
   size_t lds;
 };
 
+// Does a call run faster on the general kernel than on these windowed lanes?
+// (FP32 + refinement does not, with its two or more passes.)
+bool general_takes(const Plan &p, const Geo &g, const WinLayout &wl, bool stencil, int64_t blocks) {
+  const bool strided = g.rs != 1;
+  if (p.precision != CB_FP64 || p.P != 1 || p.desc.partitions > 1 || (strided && p.strided_wg)) return false;
+  const SegPlan &sp = p.segs[strided ? p.seg_s : 0];
+  RouteCase c;
+  c.r = p.R;
+  c.n = p.n;
+  c.strided = strided;
+  c.stencil = stencil;
+  c.rows = wl.rows != 0;
+  c.cyclic = p.desc.cyclic != 0;
+  c.uniform = sp.uniform != 0;
+  c.gM = sp.M;
+  c.gL = sp.L;
+  c.M = wl.M;
+  c.L = wl.L;
+  c.extra = wl.extra;
+  c.lines = g.nlines;
+  c.blocks = blocks;
+  c.run = g.su == 1 && (g.nlines <= g.nu || g.sv == g.nu);
+  c.cus = cu_count();
+  return general_is_faster(c);
+}
+
 // Sets up the windowed-lane launch of these lines; false when the plan has no
-// such layout for their row stride or it does not fit this call (lines whose
-// neighbours are not adjacent in memory; a line in several workgroups that is
-// solved in place, since a workgroup reads rows that another one writes).
+// such layout for their row stride, the general kernel is faster or it does not
+// fit this call (lines whose neighbours are not adjacent in memory; a line in
+// several workgroups that is solved in place, since a workgroup reads rows that
+// another one writes).
 // How: a solve or fused derivative by itself, as an item of a batched launch
 // (plain solves take the identity stencil), or the same data moved without
 // arithmetic; whether a call runs this way does not depend on it.
@@ -522,6 +550,7 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
     a.run = several ? (int)std::min<int64_t>(3, std::max<int64_t>(1, ltiles / 1024)) : 1;
     w.blocks = (ltiles + a.run - 1) / a.run;
   }
+  if (how != WIN_COPY && a.nch == 1 && general_takes(p, g, wl, st != nullptr, w.blocks)) return false;
   // Chunks of whole cache lines in fields that the 256 MB memory-side cache does
   // not hold (input and output): launch order, and where rows lie 32 KB or more
   // apart the same chunk of neighbouring lines first, so that the workgroups in
@@ -1127,7 +1156,8 @@ cb_status cb_copy_lines(cb_plan_t plan, const cb_grid *grid, int32_t axis, const
   if (overlap(in, out, span_elems(grid))) return fail(CB_ERR_INVALID_ARG, "in and out overlap");
   const bool in_parts = g.rs != 1 && plan->p.strided_wg;  // refused by launch_line
   WinLaunch w;
-  if (!in_parts && win_config(plan->p, g, in, out, nullptr, WIN_COPY, w))
+  if (!in_parts && win_config(plan->p, g, in, out, nullptr, WIN_SINGLE, w) &&
+      win_config(plan->p, g, in, out, nullptr, WIN_COPY, w))
     return launch_win(w, static_cast<hipStream_t>(stream));
   return launch_line(plan->p, g, in, out, nullptr, static_cast<hipStream_t>(stream), nullptr, true);
 }

@@ -931,9 +931,10 @@ int auto_refine_iters(const cb_plan_desc &d) {
 // with 16, 252 with 8), 8 rows where that leaves wavefronts full (n = 64 343 against
 // 286 with 16).  Unit-stride lanes that fill a wavefront's 64 (pentadiagonal
 // n = 128 8 / 16 rows 224 / 205, n = 256 16 / 12 rows 203 / 189).  Where the general
-// kernel was as fast it stays: uniform tridiagonal unit-stride lines of up to 256
-// rows (n = 128 316 against 312), others and heptadiagonal ones of up to 64 (175
-// against 148).
+// kernel was as fast it stays: tridiagonal unit-stride lines of up to 256 rows that
+// 12 does not divide (n = 128 316 against 312, n = 250 286 against 259), heptadiagonal
+// ones of less than 128 (n = 80 149 against 118) unless they fill a wavefront's lanes,
+// and others of up to 64.
 static void choose_windows(const cb_plan_desc &d, Plan &p) {
   if (d.rows_per_lane || d.lines_per_wg || d.block_barriers || d.x_staging || d.interior) return;
   if (d.precision == CB_FP32) return;
@@ -964,10 +965,11 @@ static void choose_windows(const cb_plan_desc &d, Plan &p) {
       if (&w == &p.wx && w.M && !fits(w.M, w.D)) w = WinLayout();
     };
     const int by12 = n % 12 == 0 ? 12 : 0, by16 = n % 16 == 0 ? 16 : 0;
-    if (R == 1 && n > 128 && (by12 || n > 256 || !p.segs[0].uniform))
+    if (R == 1 && n > 128 && (by12 || n > 256))
       rows({by12, n % 8 == 0 && n <= 512 ? 8 : 0, 12, 16, 8}, p.wx);
     if (R == 2 && n > 64) rows({n % 8 == 0 && n <= 128 ? 8 : 0, n >= 256 ? by16 : 0, 12, 16, 8}, p.wx);
-    if (R == 3 && n > 64) rows({by12 && 64 % (n / 12) == 0 ? 12 : 0, 16, 12}, p.wx);
+    const bool fills = by12 && 64 % (n / 12) == 0;
+    if (R == 3 && n > 64 && (fills || n >= 128)) rows({fills ? 12 : 0, 16, 12}, p.wx);
     if (R < 3) rows({n <= 384 ? by12 : 0, n % 64 == 0 && n <= 256 ? 8 : 0, by16, 16, 12, 8}, p.ws);
     if (R == 3 && n > 64) rows({by12, n > 128 ? 12 : 0, 16, 12}, p.ws);
     return;

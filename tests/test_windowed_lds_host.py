@@ -44,8 +44,8 @@ def run(driver, cases):
 # Launches, then r and n of the items.  Lanes of two sizes whose window table has
 # more words than the item's workgroup has threads, beside a wider workgroup;
 # lanes of one size (another instance, another launch); tables that fit.
-MIXED = [(1, 2, 125, 613), (1, 2, 126, 500), (1, 2, 143, 613), (1, 2, 159, 613), (1, 3, 250, 500), (2, 2, 128, 613),
-         (1, 2, 613, 125), (2, 2, 125, 613, 45), (1, 1, 401, 613)]
+MIXED = [(1, 2, 217, 613), (1, 2, 233, 500), (1, 2, 143, 613), (1, 2, 159, 613), (1, 3, 300, 613), (2, 2, 128, 613),
+         (1, 2, 613, 217), (2, 2, 217, 613, 45), (1, 1, 401, 613)]
 
 
 @pytest.mark.parametrize("form", [1, 2], ids=["per_tile", "queue"])
@@ -58,8 +58,8 @@ def test_batches_of_unlike_workgroups(driver, form):
 
 
 # short acyclic lines, whose window would be wider than the line, and longer ones
-ACYCLIC = [(1, 22), (1, 24), (1, 32), (1, 40), (1, 44), (1, 60), (2, 24), (2, 32), (2, 45), (2, 60), (2, 63), (2, 64),
-           (2, 72), (2, 128), (3, 32), (3, 64), (3, 80)]
+ACYCLIC = [(1, 22), (1, 24), (1, 32), (1, 40), (1, 44), (1, 60), (2, 24), (2, 32), (2, 45), (2, 60), (2, 63),
+           (2, 72), (2, 100), (3, 48), (3, 288)]
 
 
 @pytest.mark.parametrize("axis", [1, 2])
