@@ -477,7 +477,9 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
   // rows that are whole 128-byte lines stream past the caches; others share
   // lines with their neighbours, which the caches then serve (the strided
   // tenth-order derivative on planes of odd extent: 247 -> 285 GDOF/s)
-  const bool whole = g.su == 1 && (g.nlines <= g.nu || (g.nu % 16 == 0 && g.sv % 16 == 0)) && g.rs % 16 == 0 &&
+  // (lines in one run across planes are one row of lines, however short a plane's)
+  const bool run = g.nlines <= g.nu || g.sv == g.nu;
+  const bool whole = g.su == 1 && (run || (g.nu % 16 == 0 && g.sv % 16 == 0)) && g.rs % 16 == 0 &&
                      (uintptr_t)in % 128 == 0 && (uintptr_t)out % 128 == 0;
   if (mode == MODE_X) {
     const int QP = (Q + 1) & ~1;
