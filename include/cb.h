@@ -257,7 +257,8 @@ typedef struct {
  * Launches that share a
  * workspace must not overlap in time.  `max_ctas` >= 0 selects the
  * persistent form and caps its resident workgroups (0 = as many as fit on
- * the device at once); a negative value launches one workgroup per tile
+ * the device at once; kernel classes of windowed lanes or of one item then
+ * run without the queue); a negative value launches one workgroup per tile
  * instead (each item's tiles in the order its single launch would take;
  * measured the faster form). */
 size_t cb_batch_workspace_size(int32_t n_items);

@@ -1,6 +1,6 @@
 """Launch shapes on a device of 256 compute units, by the library's launch code on
 the host: strided lines that form one run across planes are tiled alike however
-many of them lie in a plane."""
+many of them lie in a plane; batches on the persistent queue."""
 import os
 import subprocess
 
@@ -51,7 +51,7 @@ int main() {
     cb_stencil st = {-2, 2, {1, 2, 0, 2, 1}};
     cb_batch_item it = {p, &st, g, 2, (double *)base, (double *)(2 * base)};
     std::vector<char> ws(cb_batch_workspace_bytes(&it, 1));
-    if (batch ? cb_solve_batched(&it, 1, ws.data(), ws.size(), 0, nullptr)
+    if (batch ? cb_solve_batched(&it, 1, ws.data(), ws.size(), batch == 1 ? 0 : 64, nullptr)
               : cb_solve(p, &g, 2, (double *)base, (double *)(2 * base), nullptr))
       return 1;
     cb_plan_destroy(p);
@@ -88,3 +88,10 @@ def shapes(tmp_path_factory):
 def test_runs_of_lines(shapes, n):
     got = shapes([(n, nx, 8192 // nx, 0) for nx in (1, 2, 4, 8, 16, 64, 8192)])
     assert len(set(got)) == 1, got
+
+
+def test_persistent_grid(shapes):
+    """A batch of windowed lanes (tiles of 32 lines): a workgroup per tile where as many may run as the device holds,
+    else no more than asked for and no more than tiles."""
+    cases = [(300, 16, ny, batch) for batch in (1, 2) for ny in (2, 20, 4000)]
+    assert [int(s.split()[0]) for s in shapes(cases)] == [1, 10, 2000, 1, 10, 64]
