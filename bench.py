@@ -88,6 +88,11 @@ def kernel_group(plan, axis):
     return "k_line %s/%s" % (name, "elim" if elim else "pcr")
 
 
+def refinements(plan, axis):
+    """Refinement iterations of launches along `axis`: none on windowed lanes, which solve in FP64."""
+    return 0 if windowed_rows(plan, axis) else plan.info()["refine_iters"]
+
+
 def scheme_stencil(name, n):
     """cb.Stencil of a named compact scheme's right-hand side for lines of n points."""
     return cb.Stencil(*schemes.stencil(name, n))
@@ -332,7 +337,7 @@ def leg_two_level(steps, warmup):
             torch.cuda.synchronize()
             res["n8192_P16_x_fp32_refine"] = {
                 "ms": round(ms32, 4), "gdofs": round(b.numel() / (ms32 * 1e-3) / 1e9, 2),
-                "refine_iters": plan32.info()["refine_iters"],
+                "refine_iters": refinements(plan32, ax),
                 "max_rel_diff_vs_fp64": float(((x32 - x).abs().max() / x.abs().max()).item())}
     plan.close()
     plan32.close()
@@ -475,7 +480,7 @@ def batched_runs(variants, steps, warmup, batch_ctas=-1, tune=False, extras=True
         ms = float(np.median(dur))
         r = {"ms": round(ms, 4), "gdofs": round(dof / (ms * 1e-3) / 1e9, 2),
              "hbm_gbs_algorithmic": round(16 * dof / (ms * 1e-3) / 1e9, 1), "items": len(items),
-             "refine_iters": sorted({pl.info()["refine_iters"] for pl in item_plans}),
+             "refine_iters": sorted({refinements(pl, it[4]) for pl, it in zip(item_plans, items)}),
              "outputs": [it[3] for it in items]}
         if tuned is not None:
             tuned["automatic_gdofs"] = round(dof / (tuned["automatic_ms"] * 1e-3) / 1e9, 2)

@@ -272,7 +272,10 @@ cb_status cb_solve_batched(const cb_batch_item *items, int32_t n_items, void *wo
 
 /* Read-only description of a plan's decomposition, for tests and tuning. */
 typedef struct {
-  int32_t r, n, cyclic, precision, refine_iters;
+  int32_t r, n, cyclic, precision, refine_iters; /* (iterations of launches that
+                              refine: those on windowed lanes, which array 13
+                              of cb_plan_get_array tells, solve in FP64 and run
+                              none) */
   int32_t partitions;      /* P workgroup partitions */
   int32_t lanes;           /* L lanes (sub-partitions) per segment; this and the
                               layouts below describe the general kernels:

@@ -45,3 +45,18 @@ def test_window_array():
     with pytest.raises(cb.CbError):
         plan.array(14)
     plan.close()
+
+
+@pytest.mark.parametrize("scheme,count", [("tri6", 1), ("penta10", 2)])
+def test_refinements(scheme, count):
+    """Refinement iterations as the launches run them: none where they solve in FP64."""
+    bands = schemes.bands(scheme)
+    plan = cb.Plan(bands, 500, precision="fp32_refine", host_only=True)
+    assert plan.info()["refine_iters"] == count and [bench.refinements(plan, ax) for ax in range(3)] == [0, 0, 0]
+    plan.close()
+    plan = cb.Plan(bands, 512, precision="fp32_refine", rows_per_lane=8, host_only=True)
+    assert [bench.refinements(plan, ax) for ax in range(3)] == [count] * 3
+    plan.close()
+    plan = cb.Plan(bands, 512, host_only=True)
+    assert bench.refinements(plan, 1) == 0
+    plan.close()
