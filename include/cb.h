@@ -29,6 +29,10 @@
  *   - Arguments are validated before anything is enqueued; on an error no
  *     output is written, the call returns a non-zero cb_status and
  *     cb_last_error() holds a message.  No C++ exception crosses the ABI.
+ *   - A NaN or infinity in the input reaches its own line only.  How much of
+ *     the line it reaches depends on the kernel that runs: at least the rows
+ *     around it (windowed lanes leave out what is below 2^-57 of a row's
+ *     absolute sum), at most all of them.
  *   - A plan may be used from several host threads and streams at once; it
  *     is read-only after cb_plan returns.  Calls that write the same output
  *     on different streams race, as any two kernels would.

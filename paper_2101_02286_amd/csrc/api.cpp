@@ -554,12 +554,16 @@ bool win_config(const Plan &p, const Geo &g, const double *in, double *out, cons
     w.blocks = (ltiles + a.run - 1) / a.run;
   }
   if (how != WIN_COPY && a.nch == 1 && general_takes(p, g, wl, st != nullptr, w.blocks)) return false;
-  // Chunks of whole cache lines in fields that the 256 MB memory-side cache does
-  // not hold (input and output): launch order, and where rows lie 32 KB or more
-  // apart the same chunk of neighbouring lines first, so that the workgroups in
-  // flight read long runs of each row (n = 8192, 64 x 64 lines, z 208 -> 301
-  // GDOF/s, P = 16 or not; n = 2048 on 256 x 64 y 296 -> 317, z 248 -> 303; smaller
-  // fields run best grouped, n = 4096 on 64 x 64 y 392 against 364)
+  // Chunks of whole cache lines in fields of more than 160 MB (input; as much
+  // output, against 256 MB of memory-side cache): launch order, and where rows lie
+  // 32 KB or more apart the same chunk of neighbouring lines first, so that the
+  // workgroups in flight read long runs of each row.  Lines of 2048-8192 rows in
+  // planes of 64 and 128 lines, time in launch order over grouped: median 1.08-1.10
+  // (1.05-1.19) at 59-100 MB, 1.07-1.11 (0.99-1.23) at 109-134 MB, 1.04 (0.97-1.12)
+  // at 138-155 MB.  Above the line, grouped over launch order along z: median 1.02
+  // (0.94-1.13) at 159-168 MB, 1.04-1.20 (0.98-1.29) at 172-230 MB, 1.06-1.08
+  // (0.97-1.55) at 260-400 MB (n = 2048 on 64 x 255 105 us against 159); along y
+  // either way, 0.92-1.08.
   if (mode == MODE_S && a.nch > 1 && whole && p.desc.tile_order == 0 && (double)g.n * g.nlines * 8 > 160e6) {
     a.xcds = 1;
     a.chunk_fast = g.rs >= 4096 ? 0 : 1;

@@ -897,8 +897,9 @@ int auto_refine_iters(const cb_plan_desc &d) {
   return k;
 }
 
-// Windowed lanes of a plan with constant bands whose launch shape is left to
-// the library (p.wx: unit-stride launches, p.ws: strided ones).
+// Windowed lanes of a plan whose launch shape is left to the library (p.wx:
+// unit-stride launches, p.ws: strided ones).  Which calls then run on them and
+// which on the general kernels is decided for each call (route.h).
 //
 // Unit-stride lines (a wavefront holds up to 64 lanes of one or more lines):
 // lines that also split into 2^k lanes of a kernel's row count keep that

@@ -105,9 +105,10 @@ struct RedProgram {
 // The reduced system of Eqs. (18)-(21) couples neighbouring lanes by factors
 // that decay with the rows between them, so its inverse is kept as a window:
 //   g       [rows][2D+1][R][R]: x~_l = sum_{|d| <= D} g[d] b^_{l+d}; the
-//           entries left out sum to at most 2^-57 of a row's absolute sum
-//           (2^-31 in FP32), below the rounding of the sum itself.  gidx[l] is
-//           lane l's row (lanes whose neighbourhood of sizes is alike share it).
+//           entries left out sum to at most 2^-57 of a row's absolute sum, each
+//           entry weighed by the band row that it multiplies, below the rounding
+//           of the sum itself.  gidx[l] is lane l's row (lanes whose neighbourhood
+//           of sizes is alike share it).  In an acyclic line D < L.
 // ---------------------------------------------------------------------------
 struct WinLayout {
   int M = 0, L = 0, base = 0, extra = 0, D = 0;  // M = 0: no such layout
