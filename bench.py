@@ -37,7 +37,7 @@ BYTES_PER_DOF = 16
 # HBM bytes per launch measured with rocprofv3 FETCH_SIZE / WRITE_SIZE (scaled
 # by what the counters read for a plain copy of known size); reported only
 # while the kernel sources hash to what was profiled
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_line_deriv6_512cubed_hbm_bytes.txt")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "deriv6_512cubed_hbm_bytes.txt")
 
 
 def csrc_hash():
