@@ -405,6 +405,8 @@ bool general_takes(const Plan &p, const Geo &g, const WinLayout &wl, bool stenci
   c.blocks = blocks;
   c.run = g.su == 1 && (g.nlines <= g.nu || g.sv == g.nu);
   c.cus = cu_count();
+  // (not by the pointers: a line's bits do not depend on where the field lies)
+  c.halves = g.su == 1 && (c.run || (g.nu % 8 == 0 && g.sv % 8 == 0)) && g.rs % 8 == 0;
   return general_is_faster(c);
 }
 

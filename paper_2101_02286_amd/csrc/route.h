@@ -17,6 +17,7 @@ struct RouteCase {
   int64_t lines, blocks;                // of the call; workgroups of its windowed launch
   bool run;                             // the lines are one contiguous run
   int cus;                              // compute units of the device
+  bool halves = true;                   // rows begin and end on 64-byte halves of cache lines
 };
 
 // Lanes with coefficients of their own: a workgroup copies its lines' tables to
@@ -70,6 +71,18 @@ inline bool general_strided(const RouteCase &c) {
   const bool few = 9 * c.blocks < 4 * cu;      // latency of a tile shows
   const bool mixed = c.extra > 0 || !c.cyclic;  // lanes read window rows of their own
   const bool full = c.n > 0.94 * c.gL * c.gM;   // little of the general layout idle
+  // rows whose segments share 64-byte halves with their neighbours' (planes of 52 or 89
+  // lines): windowed lanes are faster from 2^22 points on whatever the lines (n = 96,
+  // r = 2 derivatives 1.37, n = 512, r = 3 solves 1.2-1.8, n = 127, r = 2 acyclic 1.4-2.2)
+  if (!c.halves) {
+    if (points >= 12000 * cu) return false;
+    // a tile of long lanes for every ninth compute unit or fewer: n = 500 0.63-0.65 at
+    // 17 tiles, n = 384-448 0.67-0.72 at 21 (whole halves of lines 0.97-1.2)
+    if (c.r < 3 && c.gL == 32 && c.gM < 32 && c.L >= 24 && 9 * c.blocks < cu) return true;
+    // n = 1000: 0.70-0.79 at 17 tiles, 1.17-1.26 at 65
+    if (c.r == 2 && c.gL == 64) return !c.run && 6 * c.blocks < cu;
+    if (c.r == 3 && c.gL == 8 && few && c.n <= 112) return false;  // n = 80: 1.19-1.21 at 103
+  }
   if (c.stencil && c.M == 8 && c.extra > 0 && c.n > 56 && c.n < 64) return c.r < 3 && points >= 8000 * cu;  // 0.82-0.95
   // uniform general lanes of 12 rows, derivatives: n = 96, r = 1 0.89-0.93 up to 2^21 points,
   // 1.11 at 2^24; r = 2 0.71-0.91 up to 2^22, 1.06 at 2^24
@@ -79,7 +92,7 @@ inline bool general_strided(const RouteCase &c) {
     if (twelve && c.stencil) return points < (c.n <= 384 ? 32768 : 12000) * cu;
     if (twelve) return c.n <= 192 && points < (c.n < 64 ? 20000 : 8192) * cu;       // solves, n = 48 0.87-1.0, 96 0.81-0.90
     if (!c.cyclic && c.gL <= 8 && c.n > 52 && c.blocks < cu + cu / 2) return true;  // n = 112 0.86-0.89 up to 290
-    if (!c.cyclic && c.gL <= 8 && full && c.n >= 64) return points < 32768 * cu;    // n = 64 0.81 at 2^22 points
+    if (!c.cyclic && c.gL <= 8 && full && c.n >= 64) return points < 20000 * cu;    // n = 64 0.81 at 2^22 points, n = 128 on 56-line planes 1.4 at 2^23
     if (c.extra > 0 && full && c.gL <= 8 && c.n > 64) return c.stencil || points < 8192 * cu;  // n = 124 0.82-0.97
     if (!c.cyclic && c.n == c.gL * c.gM && c.gL == 16) return points < 20000 * cu;  // n = 256 0.87-0.92, 1.2 at 2^24
     // n = 92 0.88, 200 0.88-0.93 at 2^17 points; n = 1000 0.80 up to 2^20, 1.57 at 2^22

@@ -13,12 +13,12 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 DRIVER = r"""
 #include <cstdio>
 #include "route.h"
-int main() {
+int main(int argc, char **) {
   int r, n, s, st, rows, cyc, uni, gM, gL, M, L, extra, run;
   long lines, blocks;
   while (scanf("%d %d %d %d %d %d %d %d %d %d %d %d %ld %ld %d", &r, &n, &s, &st, &rows, &cyc, &uni, &gM, &gL, &M, &L, &extra,
                &lines, &blocks, &run) == 15)
-    puts(cb::general_is_faster({r, n, !!s, !!st, !!rows, !!cyc, !!uni, gM, gL, M, L, extra, lines, blocks, !!run, 256}) ? "G" : "W");
+    puts(cb::general_is_faster({r, n, !!s, !!st, !!rows, !!cyc, !!uni, gM, gL, M, L, extra, lines, blocks, !!run, 256, argc < 2}) ? "G" : "W");
 }
 """
 # kernel, scheme, n, axis, log2 of the points, derivative or solve, lines: cyclic, acyclic, per-row
@@ -39,6 +39,15 @@ G tri6 300 x 17 solve per-row      W tri6 300 x 22 solve per-row     G penta10 3
 W penta10 300 x 22 solve per-row   G hept12 512 x 19 solve per-row   W hept12 512 x 22 solve per-row
 W penta10 300 y 17 solve per-row   G penta10 80 y 20 solve per-row   W penta10 80 y 22 solve per-row
 """
+# the same on planes of 89 lines, whose rows share 64-byte halves of cache lines
+ODD = """
+W tri6 192 y 22 deriv cyclic       G tri6 384 y 19 deriv cyclic      W penta10 96 y 22 deriv cyclic
+G penta10 96 y 20 deriv cyclic     W penta10 384 y 23 deriv cyclic   W penta10 127 y 23 deriv cyclic
+W penta10 60 y 23 deriv cyclic     G penta10 500 y 19 deriv cyclic   W penta10 1000 y 21 deriv cyclic
+W hept12 64 y 23 solve cyclic      G hept12 128 y 20 deriv cyclic    W hept12 128 y 23 deriv cyclic
+W hept12 500 y 22 deriv cyclic     W hept12 512 y 23 solve cyclic    W hept12 80 y 19 deriv cyclic
+W penta10 127 y 23 solve acyclic   W penta10 128 y 23 solve acyclic  W hept12 153 y 22 solve acyclic
+"""
 
 
 def waves(r, m, lanes, d):
@@ -49,7 +58,7 @@ def waves(r, m, lanes, d):
     return max(on, key=lambda t: t[0])[1]
 
 
-def case(scheme, n, axis, log2, kind, lines):
+def case(scheme, n, axis, log2, kind, lines, halves=True):
     bands = schemes.bands(scheme)
     r = (len(bands) - 1) // 2
     rows = lines == "per-row"
@@ -68,6 +77,8 @@ def case(scheme, n, axis, log2, kind, lines):
     count = 2 ** log2 // n
     if strided:
         pairs = 32 if lanes * 32 <= ((1024 if r == 3 else 512) if rows else 256) else 16
+        if not halves:
+            pairs = 16 if lanes * 32 > 1024 or (m == 8 and lanes > 12) else 32
         blocks = -(-(count // 2) // pairs)
     elif rows:
         blocks = -(-count // (2 * waves(r, m, lanes, d) * (64 // lanes)))
@@ -80,17 +91,30 @@ def case(scheme, n, axis, log2, kind, lines):
             info["rows_per_lane" + s], info["lanes" + s], m, lanes, extra, count, blocks, 0]
 
 
-def test_measured_points(tmp_path):
-    points = [p.split() for ln in MEASURED.strip().split("\n") for p in re.split(r" {2,}", ln.strip())]
-    args = [case(s, int(n), ax, int(t), kind, lines) for _, s, n, ax, t, kind, lines in points]
+def routes(tmp_path, table, halves):
+    """The table's points, and the same with the letters that the rule gives."""
+    points = [p.split() for ln in table.strip().split("\n") for p in re.split(r" {2,}", ln.strip())]
+    args = [case(s, int(n), ax, int(t), kind, lines, halves) for _, s, n, ax, t, kind, lines in points]
     (tmp_path / "routes.cpp").write_text(DRIVER)
     exe = str(tmp_path / "routes")
     subprocess.check_call(["g++", "-std=c++17", "-I", os.path.join(ROOT, "paper_2101_02286_amd", "csrc"),
                            str(tmp_path / "routes.cpp"), "-o", exe])
-    out = subprocess.run([exe], input="\n".join(" ".join(map(str, a)) for a in args), capture_output=True, text=True)
+    out = subprocess.run([exe] + ([] if halves else ["odd"]), input="\n".join(" ".join(map(str, a)) for a in args),
+                         capture_output=True, text=True)
     got = out.stdout.split()
-    assert len(got) == len(points) == 45
-    assert [" ".join([g] + p[1:]) for g, p in zip(got, points)] == [" ".join(p) for p in points]
+    assert len(got) == len(points)
+    return [" ".join(p) for p in points], [" ".join([g] + p[1:]) for g, p in zip(got, points)]
+
+
+def test_measured_points(tmp_path):
+    want, got = routes(tmp_path, MEASURED, True)
+    assert len(want) == 45
+    assert got == want
+
+
+def test_rows_that_share_half_lines(tmp_path):
+    want, got = routes(tmp_path, ODD, False)
+    assert got == want
 
 
 @pytest.mark.parametrize("n", [129, 200, 250, 256])
